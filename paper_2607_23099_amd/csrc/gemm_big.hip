@@ -1,24 +1,30 @@
 // Big-tile class of the grouped expert GEMMs (a6, a7) for prefill-sized token counts, where the
 // work is bound by the matrix cores rather than by the weight stream.
 //
-// One workgroup of 8 waves per CU, two per SIMD, so that one wave's MFMAs run while the other
-// waits on its moves.  A work item is (tile of up to 256 tokens of one expert, 256 weight
-// rows): for GEMM1 the rows are 128 features of W1 (gate) and the same 128 of W3 (up), so the
-// SwiGLU epilogue stays inside a wave; for GEMM2 they are 256 rows of W2.  h passes between
-// the two stage-major ([I / BK][A][BK] bf16, BK the stage width below), so that each of
-// GEMM2's token moves reads whole contiguous rows of the tile.
+// One workgroup of 4 waves per CU, one per SIMD.  A work item is (tile of up to 256 tokens of one
+// expert, 256 weight rows): for GEMM1 the rows are 128 features of W1 (gate) and the same 128 of W3
+// (up), for GEMM2 256 rows of W2.  h passes between the two stage-major ([I / 64][A][64] bf16), so
+// that each of GEMM2's token moves reads whole contiguous rows of the tile.
 //
-// Each K stage of 64 columns moves the item's token rows and weight rows into an LDS ring with
-// direct buffer -> LDS loads (no registers on the way), the moves running ahead of the MFMAs.
-// Weights land in MFMA fragment order: a fragment (16 rows x 32 columns, 1 KB of bf16) holds
-// lane l's 16 bytes at l * 16, a plain contiguous copy for fragment-packed weights; row-major
-// weights are gathered into the same order.  Tokens land as 128-byte rows with XOR-swizzled
-// 16-byte chunks.  Every operand read is one 16-byte LDS read per lane, free of bank
-// conflicts.
+// A wave owns 64 weight rows x all tokens of the tile: 2 x NN MFMA blocks of 32 x 32 (32x32x16 bf16,
+// up to 256 fp32 accumulators per lane), NN the tile's 32-token blocks with valid rows.  Its weights
+// stream from memory into registers, each fragment read by one wave only and, in fp8, decoded once;
+// a ring of 2 or 4 K stages of 64 columns keeps 16 to 32 KB per wave in flight.  GEMM1 pairs 16 gate
+// and 16 up rows in one 32-row operand, so gate and up of a feature meet in one lane.  The token
+// rows, shared by the 4 waves, move into an LDS ring of 4 stages with direct buffer -> LDS loads, as
+// 128-byte rows with XOR-swizzled 16-byte chunks; each operand read is one conflict-free 16-byte LDS
+// read per lane that feeds two MFMAs (8 KB of LDS reads per 16 MFMAs; a 2 x 4 split over 8 waves with
+// both operands in LDS read 12 KB and held two stages).
 //
-// The 8 waves tile the 256 x 256 output 2 x 4: wave (wt, wr) owns 128 tokens x 64 weight rows,
-// 2 x 4 MFMA blocks of 32 x 32 (32x32x16 bf16, 128 fp32 accumulators per lane).  Per 16-column
-// k-step a wave reads 6 KB of LDS for 8 MFMAs, i.e. 1/43 B of LDS per FLOP.
+// What bounds it.  Full tiles: the card's power.  At 512 tokens per expert (DeepSeek-V3 shape, bf16,
+// random data) the matrix cores are busy 72-74% of the cycles at a clock of 1.4 GHz; with all-zero
+// tokens the same code runs at 1.95 GHz and 1480 TF/s instead of 1160.  Every byte moved costs there,
+// so items are ordered for L2 reuse (big_order).  Short tiles: the weight stream (5.9-6.3 TB/s).
+// Per layer call, before (8 waves, both operands in a two- or three-stage LDS ring) and now:
+//   bf16, 512 tokens per expert:  GEMM1 6.94-7.12 -> 6.65-6.91 ms, GEMM2 3.87-4.08 -> 3.52-3.65 ms
+//   bf16, 64 tokens per expert:   GEMM1 2.81-2.91 -> 2.41 ms
+//   Kimi-K2 shape, T = 8192, alpha = 0.3:   GEMM1 5.6 -> 5.05 ms, GEMM2 2.84 -> 2.74 ms
+//   DeepSeek-V3 fp8, T = 16384, alpha = 0.3: GEMM1 8.1 -> 7.3 ms
 #include <type_traits>
 
 #include "common.h"
@@ -30,27 +36,38 @@ namespace {
 
 constexpr int kBigBM = 256;    // tokens per tile
 constexpr int kBigRows = 256;  // weight rows per item
-constexpr uint32_t kFrag = 1024;                              // one bf16 fragment
-constexpr int kBigMaxSk = 128;  // fp8 scale columns per row held in LDS (K <= 16384)
-constexpr int kBigThreads = 512;  // 8 waves
+constexpr uint32_t kMove = 1024;  // bytes of one token move: 64 lanes x 16
+constexpr int kBigMaxSk = 128;    // fp8 scale columns per row held in LDS (K <= 16384)
+constexpr int kBigThreads = 256;  // 4 waves
 constexpr int kBigWaves = kBigThreads / 64;
+constexpr int kBigMB = kBigRows / (32 * kBigWaves);  // 32-row weight blocks per wave
 
-// LDS ring of K stages of 64 columns: 32 KB of token rows, then the weights of the stage's two
-// 32-column halves (2 x 16 KB of bf16 fragments, 2 x 8 KB of fp8), as many stages as fit in
-// the 160 KB of a CU (2 bf16, 3 fp8 beside the per-wave scale rows).  A token row of a stage
-// is one 128-byte line, so each gathered row costs one L1 -> L2 request: the operand feed is
-// bound by that request stream rather than by bytes, and 32-column stages, with two
-// half-line requests per row and stage, ran 4-7% slower for all their deeper ring.
-template <bool FP8>
+// Items of at most this many token blocks load weights with the nontemporal hint: most are an
+// expert's only tile, which streams its weights once (a 4 GiB read runs at 7.1-7.3 TB/s with the
+// hint, 6.0-6.3 without); an expert with further tiles keeps its weights cached for them.
+constexpr int kBigNtMax = 4;
+constexpr int kBigBK = 64;          // K columns per stage: a token row of a stage is one 128-byte line
+constexpr uint32_t kBigRing = 128 * 1024;                      // LDS ring of token stages
+constexpr uint32_t kBigScaleOff = kBigRing;                    // fp8: the item's two rows of block scales
+constexpr uint32_t kBigSlotOff = kBigScaleOff + 2 * kBigMaxSk * 4;
+constexpr uint32_t kBigOrderOff = kBigSlotOff + 16;            // uint16 tile order
+constexpr int kBigMaxOrder = 8192;                             // longer lists run in list order
+constexpr size_t kBigLds = kBigOrderOff + 2 * kBigMaxOrder;
+static_assert(kBigLds <= 160 * 1024, "LDS of one CU");
+
+// Per count NN of active token blocks of 32 (1 .. 8) of an item: token moves per wave and stage, token
+// stages in the LDS ring (of 8, 16 or 32 KB each), and weight stages in the register ring (32 VGPRs
+// a stage of bf16 weights, 16 of fp8).  Up to 4 blocks leave registers for 4 bf16 stages: those tiles
+// are bound by the weight stream, their time is the bytes in flight over the memory latency.  Deeper
+// rings of either kind spill, or need more than the 63 moves that the counter can tell apart.
+template <bool FP8, int NN>
 struct BigCfg {
-  static constexpr int kBK = 64;  // K columns per stage
-  static constexpr int kBufs = FP8 ? 3 : 2;
-  static constexpr uint32_t kTok = kBigBM * kBK * 2;                               // token bytes
-  static constexpr uint32_t kWHalf = kBigRows / 16 * kFrag / (FP8 ? 2 : 1);        // weights / 32 columns
-  static constexpr uint32_t kStage = kTok + kBK / 32 * kWHalf;
-  static constexpr size_t kScaleOff = kBufs * (size_t)kStage;
-  static constexpr size_t kLds = kScaleOff + (FP8 ? kBigWaves * 2 * kBigMaxSk * 4 : 0);
-  static_assert(kLds <= 160 * 1024, "LDS of one CU");
+  static constexpr int NTOK = NN <= 2 ? 2 : NN <= 4 ? 4 : 8;
+  static constexpr uint32_t kTok = NTOK * kBigWaves * kMove;
+  static constexpr int NT = 4;
+  static constexpr int D = FP8 || NN <= 4 ? 4 : 2;
+  static constexpr int NB = NN < 4 ? NN : 4;   // token blocks of one operand set
+  static constexpr int NH = NN > 4 ? 2 : 1;    // operand sets per 16-column k-step
 };
 
 typedef __attribute__((address_space(3))) uint8_t lds_t;
@@ -60,15 +77,10 @@ __device__ __forceinline__ void dma16(__amdgpu_buffer_rsrc_t r, lds_t* dst, uint
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)dst, 16, voff, soff, 0, 0);
 }
 
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint4 lds_read16(const lds_t* p) {
   return __builtin_bit_cast(uint4, *reinterpret_cast<const __attribute__((address_space(3))) u32x4*>(p));
-}
-
-__device__ __forceinline__ uint2 lds_read8(const lds_t* p) {
-  return __builtin_bit_cast(uint2, *reinterpret_cast<const __attribute__((address_space(3))) u32x2*>(p));
 }
 
 // s_waitcnt vmcnt(VM) lgkmcnt(LGKM) (gfx9 encoding; expcnt left alone).
@@ -78,60 +90,112 @@ __device__ __forceinline__ void wait_cnt() {
   __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (LGKM << 8) | ((VM >> 4) << 14));
 }
 
+// Tile order of a launch: by falling count of 32-token blocks, list order within a count (a stable
+// counting sort, one per workgroup).  The items an XCD runs at one time then take equally long, so
+// its workgroups stay at the same K stage and share its L2: the feature blocks of a tile its token
+// rows, the tiles of an expert its weights.  In list order short and long tiles alternate, the
+// workgroups drift apart and most reads miss.
+__device__ __forceinline__ int big_class(int2 en) { return 8 - min(8, max(1, ((en.y >> 16) + 31) / 32)); }
+
+__device__ __forceinline__ void big_order(const int2* __restrict__ ent, int n, lds_t* lds) {
+  typedef __attribute__((address_space(3))) uint16_t lds_u16;
+  typedef __attribute__((address_space(3))) uint32_t lds_u32;
+  lds_u16* const order = reinterpret_cast<lds_u16*>(lds + kBigOrderOff);
+  lds_u32* const cnt = reinterpret_cast<lds_u32*>(lds);  // [8 classes][threads], in the idle ring
+  const int tid = threadIdx.x, per = (n + kBigThreads - 1) / kBigThreads;
+  const int i0 = min(n, tid * per), i1 = min(n, i0 + per);
+#pragma unroll
+  for (int c = 0; c < 8; ++c) cnt[c * kBigThreads + tid] = 0;
+  for (int i = i0; i < i1; ++i) ++cnt[big_class(ent[i]) * kBigThreads + tid];
+  __syncthreads();
+  // Exclusive prefix over (class, thread): 8 counts per thread, then across the threads.
+  lds_u32* const part = cnt + 8 * kBigThreads;
+  uint32_t v[8], sum = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    v[j] = cnt[8 * tid + j];
+    sum += v[j];
+  }
+  part[tid] = sum;
+  __syncthreads();
+  uint32_t base = 0;
+  for (int t = 0; t < tid; ++t) base += part[t];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    cnt[8 * tid + j] = base;
+    base += v[j];
+  }
+  __syncthreads();
+  for (int i = i0; i < i1; ++i) order[cnt[big_class(ent[i]) * kBigThreads + tid]++] = (uint16_t)i;
+  __syncthreads();
+}
+
+// The kernel's arguments, read again from the argument segment by every item: held in registers over
+// an item's K loop they spill, and the spilled registers' reloads land in the loop.
+typedef const __attribute__((address_space(4))) GemmArgs* args_ptr;
+__device__ __forceinline__ args_ptr item_args() {
+  args_ptr p = (args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
 // mx: GEMM1 of the fp8-MFMA variant (fp8 weights only): h is rounded to bf16 as for the other
 // variants, then quantised to e4m3 with one E8M0 scale per 32 features of a row, into out
 // (codes [N / 64][A][64]) and o8s (scale words [N / 64][A][4]), the operand of its fp8-MFMA
 // GEMM2, stored stage-major so that each of GEMM2's moves reads contiguous bytes.
 template <bool GLU, bool FP8, bool PK>
-__device__ __forceinline__ void big_body(const GemmArgs& a, lds_t* lds, bool mx) {
+__device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx) {
   constexpr int FEAT = GLU ? kBigRows / 2 : kBigRows;  // output features per item
   constexpr int EB = FP8 ? 1 : 2;
-  using Cfg = BigCfg<FP8>;
-  constexpr int BK = Cfg::kBK;
-  constexpr int NTOK = Cfg::kTok / kFrag / kBigWaves;  // token DMAs per wave per stage
-  constexpr int NWDMA = FP8 ? 1 : 2;                   // weight DMAs per wave per 32 columns
-  constexpr int D = NTOK + NWDMA * BK / 32;            // vector-memory ops per pipeline iteration
-  constexpr int NB = Cfg::kBufs;
-  constexpr uint32_t SB = Cfg::kStage;
+  constexpr int BK = kBigBK;
   using WRaw = typename std::conditional<FP8, uint2, uint4>::type;
+  typedef const __attribute__((address_space(1))) uint8_t* gptr;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wt = wave >> 2, wr = wave & 3;  // token half, weight-row quarter of the output
-  const int32_t* __restrict__ list = a.tiles.list[4];
-  const int n_tiles = tile_count(list, a);
+  const int32_t* __restrict__ list = ka.tiles.list[4];
+  const int n_tiles = tile_count(list, ka);
   const int2* __restrict__ ent = reinterpret_cast<const int2*>(list + 2);
-  const int K = a.K, N = a.N;
-  const int n_fb = (N + FEAT - 1) / FEAT;
-  const int nst = K / BK;
-  const uint8_t* __restrict__ wa = reinterpret_cast<const uint8_t*>(a.wa);
-  const uint8_t* __restrict__ wb = reinterpret_cast<const uint8_t*>(a.wb);
-  const int lr = lane & 15, lg = lane >> 4, l32 = lane & 31, lh = lane >> 5;
-  const ItemMap map(n_tiles, n_fb);
+  const int n_fb = (ka.N + FEAT - 1) / FEAT;
+  const int l32 = lane & 31, lh = lane >> 5;
+  const ItemMap map(n_tiles, n_fb, GLU);
+  const bool sorted = GLU && n_tiles <= kBigMaxOrder && n_tiles * n_fb > (int)gridDim.x;
+  if (sorted) big_order(ent, n_tiles, lds);
 
   // Items come from the per-XCD work queues.  Thread 0 takes the tickets, one item ahead, and
-  // hands each to the workgroup through an LDS word of ring buffer NB - 1, which is idle from
-  // the end of an item's K loop until the first iteration of the next item's loop.
-  QueueTaker taker(a.ctrl);
+  // hands each to the workgroup through an LDS word.
+  QueueTaker taker(ka.ctrl);
   typedef volatile __attribute__((address_space(3))) int32_t lds_i32;
-  lds_i32* const slot = reinterpret_cast<lds_i32*>(lds + (NB - 1) * SB);
+  lds_i32* const slot = reinterpret_cast<lds_i32*>(lds + kBigSlotOff);
   int next = 0;
   if (tid == 0) slot[0] = taker.take(map);
   __syncthreads();
 
   for (;;) {
-    const int cur = slot[0];
+    const int cur = __builtin_amdgcn_readfirstlane(slot[0]);
     __syncthreads();  // every wave has read the ticket before thread 0 may replace it
     if (cur < 0) break;
     if (tid == 0) next = taker.take(map);  // the next ticket, while this item runs
     int tile = 0, fb = 0;
     bool ok = map.item(cur >> 28, cur & 0x0FFFFFFF, n_tiles, tile, fb);
+    if (ok && sorted) tile = reinterpret_cast<const __attribute__((address_space(3))) uint16_t*>(lds + kBigOrderOff)[tile];
     const int2 en = ok ? ent[tile] : make_int2(0, 0);
-    const int p0 = en.x, e = en.y & 0xFFFF, rows = en.y >> 16;
-    if (ok && (p0 < 0 || rows <= 0 || rows > kBigBM || p0 + rows > a.A || e >= a.E)) {
-      if (tid == 0) atomicOr(&a.ctrl[0], DAMOE_DEVERR_TILES);
+    const int p0 = __builtin_amdgcn_readfirstlane(en.x);
+    const int e = __builtin_amdgcn_readfirstlane(en.y & 0xFFFF), rows = __builtin_amdgcn_readfirstlane(en.y >> 16);
+    if (ok && (p0 < 0 || rows <= 0 || rows > kBigBM || p0 + rows > ka.A || e >= ka.E)) {
+      if (tid == 0) atomicOr(&ka.ctrl[0], DAMOE_DEVERR_TILES);
       ok = false;
     }
-    if (ok) {
+
+    // One item whose valid rows fill NN token blocks of 32.
+    auto run_item = [&](auto nn_c) __attribute__((always_inline)) {
+    constexpr int NN = decltype(nn_c)::value;
+    using Cfg = BigCfg<FP8, NN>;
+    constexpr int NTOK = Cfg::NTOK, NT = Cfg::NT, D = Cfg::D, NB = Cfg::NB, NH = Cfg::NH;
+    constexpr int NS = 4 * NH;  // operand sets per stage
+    const args_ptr a = item_args();
+    const int K = a->K, N = a->N, A = a->A;
+    const int nst = K / BK;
+
     // Token moves of this wave (padding rows read as zero).  GEMM1 gathers rows perm[p] / k of
     // x; GEMM2 reads h stage-major ([K / BK][A][BK], as this kernel's GEMM1 writes it), whose
     // rows of one stage are contiguous, through a resource per stage over the tile's rows.
@@ -139,260 +203,295 @@ __device__ __forceinline__ void big_body(const GemmArgs& a, lds_t* lds, bool mx)
     // row r = 8 (NTOK wave + j) + l / 8, its 16-byte chunk c = (l % 8) ^ ((r / 2) % 8), which
     // lands at slot l % 8 of the row.  The swizzle puts the 16 rows that one read phase of an
     // MFMA operand touches on 16 distinct bank groups.
-    const int p0u = __builtin_amdgcn_readfirstlane(p0), rowsu = __builtin_amdgcn_readfirstlane(rows);
-    __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, GLU ? (uint32_t)((size_t)(a.A / a.k) * K * 2) : 0u);
+    const uint32_t xbytes = (uint32_t)((size_t)(A / a->k) * K * 2);
     uint32_t xo[NTOK];
 #pragma unroll
     for (int j = 0; j < NTOK; ++j) {
       const int r = 8 * (NTOK * wave + j) + (lane >> 3);
       const uint32_t cb = (uint32_t)(((lane & 7) ^ ((r >> 1) & 7)) * 16);
       if (r < rows) {
-        xo[j] = GLU ? (uint32_t)(a.perm[p0 + r] / a.k) * (uint32_t)K * 2u + cb : (uint32_t)r * (BK * 2u) + cb;
+        xo[j] = GLU ? (uint32_t)(a->perm[p0 + r] / a->k) * (uint32_t)K * 2u + cb : (uint32_t)r * (BK * 2u) + cb;
       } else {
         xo[j] = kOobOffset;
       }
     }
-    // Weight fragments this wave moves: item row blocks 2 * wave, 2 * wave + 1.  GEMM1: item
-    // blocks 0..7 are W1 features fb * 128 + 16 b, blocks 8..15 the same features of W3.  An fp8
-    // fragment is 512 B, so one move carries both row blocks (lanes 0..31 and 32..63).
+    // Moves of stages past the last go through an empty resource: they read no memory, and the
+    // counts of moves in flight stay the same.
+    auto dma_tok = [&](int st, lds_t* sb) __attribute__((always_inline)) {
+      const bool in = st < nst;
+      const uint32_t s0 = in ? st : 0;
+      const __amdgpu_buffer_rsrc_t rx =
+          GLU ? make_rsrc(a->x, in ? xbytes : 0u)
+              : make_rsrc(a->x + ((size_t)s0 * A + p0) * BK, in ? (uint32_t)rows * (BK * 2u) : 0u);
+#pragma unroll
+      for (int j = 0; j < NTOK; ++j) dma16(rx, sb + (NTOK * wave + j) * kMove, xo[j], GLU ? s0 * (BK * 2u) : 0u);
+    };
+
+    // Weight operand of this wave: 32 rows, lane l row l % 32, 8 columns 8 (l / 32) .. of a
+    // 16-column k-step.  GEMM1: rows 0..15 are W1 features fb * 128 + 16 wave .., rows 16..31 the
+    // same features of W3, so gate and up of a feature meet in one lane.  GEMM2: W2 rows
+    // fb * 256 + 32 wave ..; a last item of 128 rows repeats row blocks (never stored).
     const size_t slab = (size_t)N * K * EB;
-    const __amdgpu_buffer_rsrc_t rw =
-        make_rsrc(((GLU && wave >= 4) ? wb : wa) + (size_t)e * slab, (uint32_t)slab);
-    const uint32_t rb0 = GLU ? (uint32_t)fb * 8u + (wave & 3) * 2u : (uint32_t)fb * 16u + wave * 2u;
-    uint32_t wo[NWDMA];
+    gptr wp[kBigMB], wps[kBigMB];
 #pragma unroll
-    for (int j = 0; j < NWDMA; ++j) {
-      if (FP8) {
-        const uint32_t rbg = rb0 + 2 * j + lh;
-        if (PK) wo[j] = rbg * (uint32_t)(K / 32) * 512u + l32 * 16u;
-        else wo[j] = (rbg * 16u + lr) * (uint32_t)K + (lg & 1) * 16u;
-      } else {
-        const uint32_t rbg = rb0 + j;
-        if (PK) wo[j] = (rbg * (uint32_t)(K / 32) * 64u + lane) * 16u;
-        else wo[j] = ((rbg * 16u + lr) * (uint32_t)K + lg * 8u) * 2u;
-      }
+    for (int m = 0; m < kBigMB; ++m) {
+      const uint32_t rb = GLU ? (uint32_t)(fb * 8 + wave * kBigMB + m)
+                              : (uint32_t)min(fb * 16 + (wave * kBigMB + m) * 2 + (l32 >> 4), N / 16 - 1);
+      const size_t woff = (size_t)e * slab + (PK ? (size_t)rb * (K / 32) * (512 * EB) + ((l32 & 15) + 16 * lh) * 8 * EB
+                                                 : ((size_t)(rb * 16 + (l32 & 15)) * K + 8 * lh) * EB);
+      wp[m] = (gptr)((GLU && (l32 >> 4)) ? a->wb : a->wa) + woff;
     }
-    auto dma_stage = [&](int st, lds_t* sb) __attribute__((always_inline)) {
-      if (!GLU) rx = make_rsrc(a.x + ((size_t)st * a.A + p0u) * BK, (uint32_t)rowsu * (BK * 2u));
+    constexpr uint32_t kWStage = PK ? 1024 * EB : BK * EB;  // bytes from one stage to the next
+    WRaw wf[D][4][kBigMB];
+    auto wstage = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
-      for (int j = 0; j < NTOK; ++j) dma16(rx, sb + (NTOK * wave + j) * kFrag, xo[j], GLU ? (uint32_t)st * (BK * 2u) : 0u);
+      for (int m = 0; m < kBigMB; ++m) wps[m] = wp[m] + (size_t)min(st, nst - 1) * kWStage;
+    };
+    auto wload = [&](int d, int ks) __attribute__((always_inline)) {
+      typedef uint32_t vec __attribute__((ext_vector_type(sizeof(WRaw) / 4)));
+      const uint32_t off = PK ? ((ks >> 1) * 512u + (ks & 1) * 256u) * EB : ks * 16u * EB;
 #pragma unroll
-      for (int h = 0; h < BK / 32; ++h) {
-        const uint32_t s32 = (uint32_t)st * (BK / 32) + h;  // 32-column block of K
-#pragma unroll
-        for (int j = 0; j < NWDMA; ++j) {
-          const uint32_t so = FP8 ? (PK ? s32 * 512u : s32 * 32u) : (PK ? s32 * 1024u : s32 * 64u);
-          dma16(rw, sb + Cfg::kTok + h * Cfg::kWHalf + (NWDMA * wave + j) * kFrag, wo[j], so);
-        }
+      for (int m = 0; m < kBigMB; ++m) {
+        const auto* q = reinterpret_cast<const __attribute__((address_space(1))) vec*>(wps[m] + off);
+        if constexpr (NN <= kBigNtMax) wf[d][ks][m] = __builtin_bit_cast(WRaw, __builtin_nontemporal_load(q));
+        else wf[d][ks][m] = __builtin_bit_cast(WRaw, *q);
       }
     };
 
-    // fp8 block scales of this wave's rows (one 128-row block per matrix): the item's row of
-    // scale columns is staged in LDS, K stage st reads column st / 4 with its operands.
-    lds_f32* sc_lds = nullptr;
+    // fp8 block scales of the item's rows (a 128-row block per matrix of GEMM1, per half of
+    // GEMM2), one per 128 columns, staged in LDS.
+    lds_f32* const sc_lds = reinterpret_cast<lds_f32*>(lds + kBigScaleOff);
     if constexpr (FP8) {
       const int sk = K / 128;
-      const int srow = GLU ? fb : fb * 2 + (wr >> 1);
-      const bool srow_ok = srow < N / 128;
-      const size_t sbase = ((size_t)e * (N / 128) + (srow_ok ? srow : 0)) * sk;
-      lds_f32* wsc = reinterpret_cast<lds_f32*>(lds + Cfg::kScaleOff) + wave * 2 * kBigMaxSk;
-#pragma unroll
-      for (int h = 0; h < kBigMaxSk / 64; ++h) {
-        const int i = h * 64 + lane;
-        if (i < sk) {
-          wsc[i] = srow_ok ? a.sa[sbase + i] : 0.f;
-          if (GLU) wsc[kBigMaxSk + i] = srow_ok ? a.sb[sbase + i] : 0.f;
-        }
+      for (int i = tid; i < 2 * kBigMaxSk; i += kBigThreads) {
+        const int m = i / kBigMaxSk, kb = i % kBigMaxSk;
+        const int srow = GLU ? fb : min(fb * 2 + m, N / 128 - 1);
+        if (kb < sk) sc_lds[i] = ((GLU && m) ? a->sb : a->sa)[((size_t)e * (N / 128) + srow) * sk + kb];
       }
-      sc_lds = wsc;
     }
+    const lds_f32* const sc_lane = sc_lds + (GLU ? (l32 >> 4) : (wave >> 1)) * kBigMaxSk;
 
-    // Wave (wt, wr) accumulates 2 x 4 MFMA blocks of 32 x 32: block (m, n) = weight rows
-    // 32 m .. + 31 of the wave's 64 (GEMM1: m = 0 the gate features, m = 1 the same up
-    // features) x the 32 tokens of token block 2 n + wt.  Interleaving the token blocks of the
-    // two token waves splits a short tile evenly between them; a wave multiplies only its
-    // first nn blocks, those holding valid rows (rows beyond `rows` are never stored, so the
-    // blocks after them need no MFMA).
-    const int nn = min(4, max(0, ((rows + 31) / 32 - wt + 1) / 2));
-    floatx16 acc[2][4];
+    floatx16 acc[kBigMB][NN];
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < kBigMB; ++m)
 #pragma unroll
-      for (int n = 0; n < 4; ++n)
+      for (int n = 0; n < NN; ++n)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[m][n][r] = 0.f;
 
-    // Operands of one 16-column k-step (ks = 0 .. BK / 16 - 1 of a stage).  A 32x32x16 operand
-    // lane l takes row l % 32 and the 8-column chunk 2 ks + l / 32 of the stage: for weights,
-    // fragment row block (l % 32) / 16, row l % 16 in it, of the stage's 32-column half ks / 2;
-    // for tokens, the swizzled slot of that chunk in the token row.
-    struct Ops {
-      WRaw w[2];
-      uint4 t[4];
-      float sg, su;  // fp8: block scales of the stage
-    };
-    auto read_ops = [&](int ks, int st, const lds_t* cur, Ops& o, auto nn_c) __attribute__((always_inline)) {
-      constexpr int NN = decltype(nn_c)::value;
-      const int c = 2 * (ks & 1) + lh;  // chunk within the 32-column half
-      const lds_t* wcur = cur + Cfg::kTok + (ks >> 1) * Cfg::kWHalf;
-      if constexpr (FP8) {
-        o.sg = sc_lds[(st * BK) >> 7];
-        if (GLU) o.su = sc_lds[kBigMaxSk + ((st * BK) >> 7)];
-      }
+    // Token operands: lane l takes row 32 n + l % 32 of token block n and the 8-column chunk
+    // 2 ks + l / 32 of the stage, at its swizzled slot.  Set s of a stage is k-step s / NH, token
+    // blocks 4 (s % NH) .. of it.
+    uint4 tf[2][NB];
+    auto read_set = [&](int s, const lds_t* tcur, uint4 (&o)[NB]) __attribute__((always_inline)) {
+      const int ks = s / NH, n0 = 4 * (s % NH);
+      const lds_t* row = tcur + l32 * 128 + (((2 * ks + lh) ^ ((l32 >> 1) & 7)) << 4);
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        const int wrb = (GLU ? (m == 0 ? 2 * wr : 8 + 2 * wr) : 4 * wr + 2 * m) + (l32 >> 4);
-        if constexpr (FP8) {
-          const lds_t* blk = wcur + (wrb >> 1) * kFrag + (wrb & 1) * 512;
-          if (PK) o.w[m] = lds_read8(blk + (lr + 16 * c) * 8);
-          else o.w[m] = lds_read8(blk + ((ks & 1) * 16 + lr) * 16 + 8 * lh);
-        } else {
-          o.w[m] = lds_read16(wcur + wrb * kFrag + (lr + 16 * c) * 16);
+      for (int i = 0; i < NB; ++i)
+        if (n0 + i < NN) o[i] = lds_read16(row + (n0 + i) * 4096);
+    };
+    uint4 wv[kBigMB];
+    float sc = 0.f;
+    auto mma_set = [&](int s, int d, const uint4 (&o)[NB]) __attribute__((always_inline)) {
+      const int ks = s / NH, n0 = 4 * (s % NH);
+      if (n0 == 0) {
+#pragma unroll
+        for (int m = 0; m < kBigMB; ++m) {
+          if constexpr (FP8) wv[m] = fp8x8_to_bf16x8(wf[d][ks][m], sc);
+          else wv[m] = wf[d][ks][m];
         }
       }
 #pragma unroll
-      for (int n = 0; n < NN; ++n) {
-        const int r = 32 * (2 * n + wt) + l32, cc = 2 * ks + lh;
-        o.t[n] = lds_read16(cur + r * 128 + ((cc ^ ((r >> 1) & 7)) << 4));
-      }
-    };
-    auto mma = [&](const Ops& o, auto nn_c) __attribute__((always_inline)) {
-      constexpr int NN = decltype(nn_c)::value;
-      if constexpr (NN == 0) return;
+      for (int i = 0; i < NB; ++i)
+        if (n0 + i < NN)
 #pragma unroll
-      for (int m = 0; m < 2; ++m) {
-        uint4 wv;
-        if constexpr (FP8) wv = fp8x8_to_bf16x8(o.w[m], (GLU && m == 1) ? o.su : o.sg);
-        else wv = o.w[m];
-#pragma unroll
-        for (int n = 0; n < NN; ++n) acc[m][n] = mfma32x32x16(wv, o.t[n], acc[m][n]);
-      }
+          for (int m = 0; m < kBigMB; ++m) acc[m][n0 + i] = mfma32x32x16(wv[m], o[i], acc[m][n0 + i]);
     };
 
-    // Software pipeline.  Iteration t (between barriers t - 1 and t): DMA of stage t + NB - 1 into
-    // the buffer stage t - 1 left, operand reads of stage t (k-step 0 then 1) each issued
-    // ahead of the MFMAs of the previous k-step, then wait for this wave's DMAs of stage
-    // t + 1 and its LDS reads, and the barrier that makes stage t + 1 visible to every wave
-    // and frees stage t's buffer.  The barrier is a bare s_barrier: the counter waits before
-    // it are the ordering (a fence would drain the DMAs still ahead).  `dst` and `cur` are
-    // distinct buffers, so the compiler does not hold the reads of `cur` behind the DMA
-    // writes into `dst`.  Stages past the last are re-issued as the last stage into buffers
-    // nobody reads again.
-    Ops A, B;
-    auto iter = [&](lds_t* __restrict__ dst, const lds_t* __restrict__ cur, int t, auto first, auto nn_c)
+    // Software pipeline.  Iteration t (between barriers t - 1 and t): the DMA of the tokens of
+    // stage t + NT - 1 into the buffer stage t - 1 left; operand reads of stage t, each set's
+    // issued ahead of the MFMAs of the one before (the last set's MFMAs run in the next
+    // iteration); each k-step's weight registers are loaded again, for stage t + D, after its last
+    // MFMAs.  Then a wait for this wave's token moves of stage t + 1 and its LDS reads, and the
+    // barrier that makes stage t + 1 visible to every wave and frees stage t's buffer.  Moves
+    // complete in issue order: after those of stage t + 1 the wave issued the moves of NT - 2
+    // stages and the loads of NT - 1 iterations (at the start of the item, those of D stages).  The barrier is a bare
+    // s_barrier: the counter waits before it are the ordering (a fence would drain the moves
+    // still ahead).  `tdst` and `tcur` are distinct buffers, so the compiler does not hold the
+    // reads behind the moves.
+    constexpr int NW = 4 * kBigMB;  // weight loads of a stage
+    constexpr int kAhead = (NT - 2) * NTOK + (NW * (NT - 1) < NW * (D + 1) - kBigMB ? NW * (NT - 1) : NW * (D + 1) - kBigMB);
+    auto iter = [&](lds_t* __restrict__ tdst, const lds_t* __restrict__ tcur, int t, auto d_c)
         __attribute__((always_inline)) {
-      dma_stage(min(t + NB - 1, nst - 1), dst);
+      constexpr int d = decltype(d_c)::value, dp = (d + D - 1) % D;
+      dma_tok(t + NT - 1, tdst);
+      float sc_next = 0.f;
+      if constexpr (FP8) sc_next = sc_lane[(t * BK) >> 7];
 #pragma unroll
-      for (int kp = 0; kp < BK / 32; ++kp) {
-        read_ops(2 * kp, t, cur, A, nn_c);
+      for (int s = 0; s < NS; ++s) {
+        read_set(s, tcur, tf[s & 1]);
         __builtin_amdgcn_sched_barrier(0);
-        if (kp > 0 || !decltype(first)::value) mma(B, nn_c);
-        __builtin_amdgcn_sched_barrier(0);
-        read_ops(2 * kp + 1, t, cur, B, nn_c);
-        __builtin_amdgcn_sched_barrier(0);
-        mma(A, nn_c);
+        if (s == 0) {
+          if (t > 0) mma_set(NS - 1, dp, tf[1]);
+          wload(dp, 3);
+          wstage(t + D);
+          sc = sc_next;
+        } else {
+          mma_set(s - 1, d, tf[(s - 1) & 1]);
+          if (s % NH == 0) wload(d, s / NH - 1);
+        }
         __builtin_amdgcn_sched_barrier(0);
       }
-      wait_cnt<(NB - 2) * D, 0>();
+      wait_cnt<kAhead, 0>();
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
-    auto epilogue = [&](auto nn_c) __attribute__((always_inline)) {
-      constexpr int NN = decltype(nn_c)::value;
-      // Epilogue from the accumulators: in block (m, n) lane l holds token 32 (2 n + wt) + l % 32
-      // and, in registers 4 q .. 4 q + 3, weight rows 8 q + 4 (l / 32) .. + 3.
+    auto tbuf = [&](int i) __attribute__((always_inline)) { return lds + (uint32_t)(i % NT) * Cfg::kTok; };
+
+#pragma unroll
+    for (int i = 0; i < NT - 1; ++i) dma_tok(i, tbuf(i));
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      wstage(d);
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks)
+        if (d < D - 1 || ks < 3) wload(d, ks);  // the last one in iteration 0
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    wait_cnt<(NT - 2) * NTOK + NW * D - kBigMB, 15>();  // this wave's stage-0 moves have landed
+    __syncthreads();                              // ... and every wave's, and the scales
+    int t = 0;
+    auto trip = [&](auto cnt_c) __attribute__((always_inline)) {
+      constexpr int CNT = decltype(cnt_c)::value;
+      iter(tbuf(t + NT - 1), tbuf(t), t, std::integral_constant<int, 0>{});
+      iter(tbuf(t + NT), tbuf(t + 1), t + 1, std::integral_constant<int, 1>{});
+      if constexpr (CNT >= 4) {
+        iter(tbuf(t + NT + 1), tbuf(t + 2), t + 2, std::integral_constant<int, 2>{});
+        iter(tbuf(t + NT + 2), tbuf(t + 3), t + 3, std::integral_constant<int, 3>{});
+      }
+      if constexpr (CNT == 8) {
+        iter(tbuf(t + NT + 3), tbuf(t + 4), t + 4, std::integral_constant<int, 4>{});
+        iter(tbuf(t + NT + 4), tbuf(t + 5), t + 5, std::integral_constant<int, 5>{});
+        iter(tbuf(t + NT + 5), tbuf(t + 6), t + 6, std::integral_constant<int, 6>{});
+        iter(tbuf(t + NT + 6), tbuf(t + 7), t + 7, std::integral_constant<int, 7>{});
+      }
+      t += CNT;
+    };
+    // K is a multiple of 128 (512 with fp8 weights), so the stages are a multiple of 2 (8).
+    while (t + D <= nst) trip(std::integral_constant<int, D>{});
+    if (D == 4 && !FP8 && t < nst) {
+      trip(std::integral_constant<int, 2>{});
+      mma_set(NS - 1, 1, tf[1]);
+    } else {
+      mma_set(NS - 1, D - 1, tf[1]);
+    }
+    // Moves and loads past the last stage may still be in flight: drain before the next item's.
+    wait_cnt<0, 0>();
+    __syncthreads();
+
+    // Epilogue from the accumulators: in block n lane l holds token 32 n + l % 32 and, in
+    // registers 4 q .. 4 q + 3, weight rows 8 q + 4 (l / 32) .. + 3 of the wave's 32.  A swap of
+    // the lane halves between the packed words of q and q + 1 leaves 8 consecutive features in
+    // each lane: 8 (l / 32) .. + 7 of the 16.
+    const args_ptr ae = item_args();
+    const int Ne = ae->N, Ae = ae->A;
+    void* const out = ae->out;
+    auto swap = [&](uint32_t& x, uint32_t& y) __attribute__((always_inline)) {
+      const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+      x = r[0];
+      y = r[1];
+    };
+    if constexpr (GLU) {
+      float hv[kBigMB][8];
+      auto swiglu = [&](int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < kBigMB; ++m)
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const float g = acc[m][n][j], u = acc[m][n][8 + j];
+            hv[m][j] = g / (1.0f + __expf(-g)) * u;
+          }
+      };
+      const int f0 = fb * FEAT + 32 * wave;  // the wave's 32 features
 #pragma unroll
       for (int n = 0; n < NN; ++n) {
-        const int i = (2 * n + wt) * 32 + l32;
-        const size_t orow = (size_t)(p0 + i) * N;
-        if constexpr (GLU && FP8) {
+        const int i = 32 * n + l32;
+        swiglu(n);
+        if constexpr (FP8) {
           if (mx) {
-            // The wave's 32 features fb * FEAT + wr * 32 .. of token i: lane l and lane l ^ 32
-            // hold them, so the block maximum takes one exchange.
-            float hb[16];
+            // The wave's 32 features of token i are an MX block: lane l and lane l ^ 32 hold them.
             float amax = 0.f;
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-              const float g = acc[0][n][j], u = acc[1][n][j];
-              hb[j] = (float)(__bf16)(g / (1.0f + __expf(-g)) * u);
-              amax = fmaxf(amax, fabsf(hb[j]));
-            }
-            amax = fmaxf(amax, __shfl_xor(amax, 32));
-            const uint32_t sc = mx_scale_byte(amax);
-            const float inv = mx_inv_scale(sc);
-            if (i < rows) {
-              // Stage-major for GEMM2's 64-column stages: codes [N / 64][A][64], scale words
-              // [N / 64][A][4] (byte (f0 / 32) % 2; bytes 2 and 3 unused).
-              const int f0 = fb * FEAT + wr * 32;
-              const size_t srow = (size_t)(f0 / 64) * a.A + (p0 + i);
-              uint8_t* h8 = reinterpret_cast<uint8_t*>(a.out) + srow * 64 + f0 % 64;
+            for (int m = 0; m < kBigMB; ++m)
 #pragma unroll
-              for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<uint32_t*>(h8 + 8 * q + 4 * lh) =
-                    e4m3x4(hb[4 * q] * inv, hb[4 * q + 1] * inv, hb[4 * q + 2] * inv, hb[4 * q + 3] * inv);
-              if (lh == 0) a.o8s[srow * 4 + (f0 / 32) % 2] = (uint8_t)sc;
+              for (int j = 0; j < 8; ++j) {
+                hv[m][j] = (float)(__bf16)hv[m][j];
+                amax = fmaxf(amax, fabsf(hv[m][j]));
+              }
+            amax = fmaxf(amax, __shfl_xor(amax, 32));
+            const uint32_t scb = mx_scale_byte(amax);
+            const float inv = mx_inv_scale(scb);
+            // Stage-major for GEMM2's 64-column stages: codes [N / 64][A][64], scale words
+            // [N / 64][A][4] (byte (f0 / 32) % 2; bytes 2 and 3 unused).
+            const size_t srow = (size_t)(f0 / 64) * Ae + (p0 + i);
+#pragma unroll
+            for (int m = 0; m < kBigMB; ++m) {
+              uint32_t c0 = e4m3x4(hv[m][0] * inv, hv[m][1] * inv, hv[m][2] * inv, hv[m][3] * inv);
+              uint32_t c1 = e4m3x4(hv[m][4] * inv, hv[m][5] * inv, hv[m][6] * inv, hv[m][7] * inv);
+              swap(c0, c1);
+              if (i < rows)
+                *reinterpret_cast<uint2*>(reinterpret_cast<uint8_t*>(out) + srow * 64 + f0 % 64 + 16 * m + 8 * lh) =
+                    make_uint2(c0, c1);
             }
+            if (i < rows && lh == 0) ae->o8s[srow * 4 + (f0 / 32) % 2] = (uint8_t)scb;
             continue;
           }
         }
-        if (i >= rows) continue;
+        // h stage-major for this kernel's GEMM2 (its stages of BK columns): [N / BK][A][BK].
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (GLU) {
-            // h stage-major for this kernel's GEMM2 (its stages of BK columns): [N / BK][A][BK].
-            const int f = fb * FEAT + wr * 32 + 8 * q + 4 * lh;
-            if (f >= N) continue;
-            float hv[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float g = acc[0][n][4 * q + r], u = acc[1][n][4 * q + r];
-              hv[r] = g / (1.0f + __expf(-g)) * u;
-            }
-            uint2 pk;
-            pk.x = pack_bf16x2(hv[0], hv[1]);
-            pk.y = pack_bf16x2(hv[2], hv[3]);
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) +
-                                      ((size_t)(f / BK) * a.A + (p0 + i)) * BK + f % BK) = pk;
-          } else {
-#pragma unroll
-            for (int m = 0; m < 2; ++m) {
-              const int f = fb * FEAT + wr * 64 + m * 32 + 8 * q + 4 * lh;
-              if (f >= N) continue;
-              uint2 pk;
-              pk.x = pack_bf16x2(acc[m][n][4 * q], acc[m][n][4 * q + 1]);
-              pk.y = pack_bf16x2(acc[m][n][4 * q + 2], acc[m][n][4 * q + 3]);
-              *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(a.out) + orow + f) = pk;
-            }
-          }
+        for (int m = 0; m < kBigMB; ++m) {
+          uint4 pk = make_uint4(pack_bf16x2(hv[m][0], hv[m][1]), pack_bf16x2(hv[m][2], hv[m][3]),
+                                pack_bf16x2(hv[m][4], hv[m][5]), pack_bf16x2(hv[m][6], hv[m][7]));
+          swap(pk.x, pk.z);
+          swap(pk.y, pk.w);
+          if (i < rows)
+            *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(out) +
+                                      ((size_t)(f0 / BK) * Ae + (p0 + i)) * BK + f0 % BK + 16 * m + 8 * lh) = pk;
         }
       }
-    };
-    // The K loop and epilogue, one instance per count of active token blocks (each instance
-    // stores only its own blocks, so no accumulator lives across instances): every wave
-    // issues the same DMAs and meets the same barriers whatever its count.
-    auto k_loop = [&](auto nn_c) __attribute__((always_inline)) {
-      iter(lds + (NB - 1) * SB, lds, 0, std::true_type{}, nn_c);
-      for (int t = 1; t < nst; ++t)
-        iter(lds + ((t + NB - 1) % NB) * SB, lds + (t % NB) * SB, t, std::false_type{}, nn_c);
-      mma(B, nn_c);
-      // Moves of re-issued stages may still be in flight: drain before the next item's DMAs.
-      wait_cnt<0, 0>();
-      __syncthreads();
-      epilogue(nn_c);
-    };
-
+    } else {
 #pragma unroll
-    for (int st = 0; st < NB - 1; ++st) dma_stage(min(st, nst - 1), lds + st * SB);
-    wait_cnt<(NB - 2) * D, 15>();  // this wave's stage-0 moves have landed
-    __syncthreads();        // ... and every wave's (also orders the scale rows in LDS)
-    switch (nn) {
-      case 4: k_loop(std::integral_constant<int, 4>{}); break;
-      case 3: k_loop(std::integral_constant<int, 3>{}); break;
-      case 2: k_loop(std::integral_constant<int, 2>{}); break;
-      case 1: k_loop(std::integral_constant<int, 1>{}); break;
-      default: k_loop(std::integral_constant<int, 0>{}); break;
+      for (int n = 0; n < NN; ++n) {
+        const int i = 32 * n + l32;
+        uint16_t* orow = reinterpret_cast<uint16_t*>(out) + (size_t)(p0 + i) * Ne;
+#pragma unroll
+        for (int m = 0; m < kBigMB; ++m)
+#pragma unroll
+          for (int q = 0; q < 4; q += 2) {
+            const floatx16& c = acc[m][n];
+            uint4 pk = make_uint4(pack_bf16x2(c[4 * q], c[4 * q + 1]), pack_bf16x2(c[4 * q + 2], c[4 * q + 3]),
+                                  pack_bf16x2(c[4 * q + 4], c[4 * q + 5]), pack_bf16x2(c[4 * q + 6], c[4 * q + 7]));
+            swap(pk.x, pk.z);
+            swap(pk.y, pk.w);
+            const int f = fb * FEAT + (wave * kBigMB + m) * 32 + 8 * q + 8 * lh;
+            if (i < rows && f < Ne) *reinterpret_cast<uint4*>(orow + f) = pk;
+          }
+      }
     }
-    }  // ok
+    };  // run_item
+    if (ok) {
+      switch ((rows + 31) / 32) {
+        case 1: run_item(std::integral_constant<int, 1>{}); break;
+        case 2: run_item(std::integral_constant<int, 2>{}); break;
+        case 3: run_item(std::integral_constant<int, 3>{}); break;
+        case 4: run_item(std::integral_constant<int, 4>{}); break;
+        case 5: run_item(std::integral_constant<int, 5>{}); break;
+        case 6: run_item(std::integral_constant<int, 6>{}); break;
+        case 7: run_item(std::integral_constant<int, 7>{}); break;
+        default: run_item(std::integral_constant<int, 8>{}); break;
+      }
+    }
     // Every wave has read this item's ticket and its K loop has drained (or it had none).
     if (tid == 0) slot[0] = next;
     __syncthreads();
@@ -403,7 +502,6 @@ __device__ __forceinline__ void big_body(const GemmArgs& a, lds_t* lds, bool mx)
 template <bool GLU, bool FP8, bool PK>
 __global__ void __launch_bounds__(kBigThreads, 1) k_gemm_big(GemmArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t big_smem[];
-  pin_gemm_args(a);
   flag_stale_tiles(a);
   const int v = a.force_variant >= 0 ? a.force_variant : *a.variant_id;
   if (GLU && blockIdx.x == 0 && threadIdx.x == 0) a.ctrl[4] = v;
@@ -420,11 +518,11 @@ __global__ void __launch_bounds__(kBigThreads, 1) k_gemm_big(GemmArgs a) {
 template <bool GLU>
 hipError_t launch_big_stage(const GemmArgs& a, int grid, hipStream_t stream) {
   if (a.fp8) {
-    if (a.packed) hipLaunchKernelGGL((k_gemm_big<GLU, true, true>), dim3(grid), dim3(kBigThreads), BigCfg<true>::kLds, stream, a);
-    else hipLaunchKernelGGL((k_gemm_big<GLU, true, false>), dim3(grid), dim3(kBigThreads), BigCfg<true>::kLds, stream, a);
+    if (a.packed) hipLaunchKernelGGL((k_gemm_big<GLU, true, true>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
+    else hipLaunchKernelGGL((k_gemm_big<GLU, true, false>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
   } else {
-    if (a.packed) hipLaunchKernelGGL((k_gemm_big<GLU, false, true>), dim3(grid), dim3(kBigThreads), BigCfg<false>::kLds, stream, a);
-    else hipLaunchKernelGGL((k_gemm_big<GLU, false, false>), dim3(grid), dim3(kBigThreads), BigCfg<false>::kLds, stream, a);
+    if (a.packed) hipLaunchKernelGGL((k_gemm_big<GLU, false, true>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
+    else hipLaunchKernelGGL((k_gemm_big<GLU, false, false>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
   }
   return hipGetLastError();
 }
@@ -437,14 +535,14 @@ hipError_t big_set_lds_limits() {
     size_t lds;
   };
   const Fn fns[] = {
-      {reinterpret_cast<const void*>(&k_gemm_big<true, false, false>), BigCfg<false>::kLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, false, false>), BigCfg<false>::kLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<true, true, false>), BigCfg<true>::kLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, true, false>), BigCfg<true>::kLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<true, false, true>), BigCfg<false>::kLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, false, true>), BigCfg<false>::kLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<true, true, true>), BigCfg<true>::kLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, true, true>), BigCfg<true>::kLds}};
+      {reinterpret_cast<const void*>(&k_gemm_big<true, false, false>), kBigLds},
+      {reinterpret_cast<const void*>(&k_gemm_big<false, false, false>), kBigLds},
+      {reinterpret_cast<const void*>(&k_gemm_big<true, true, false>), kBigLds},
+      {reinterpret_cast<const void*>(&k_gemm_big<false, true, false>), kBigLds},
+      {reinterpret_cast<const void*>(&k_gemm_big<true, false, true>), kBigLds},
+      {reinterpret_cast<const void*>(&k_gemm_big<false, false, true>), kBigLds},
+      {reinterpret_cast<const void*>(&k_gemm_big<true, true, true>), kBigLds},
+      {reinterpret_cast<const void*>(&k_gemm_big<false, true, true>), kBigLds}};
   for (const Fn& f : fns) {
     const hipError_t e = hipFuncSetAttribute(f.f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.lds);
     if (e != hipSuccess) return e;

@@ -22,10 +22,13 @@ namespace damoe {
 constexpr int kXcds = 8;
 
 struct ItemMap {
-  bool xcd;
+  bool xcd, ends;
   int fg, tg, n_fg, nq, n_chunks;
 
-  __device__ ItemMap(int n_tiles, int n_fb) {
+  // both_ends: odd queues run their chunks from the last to the first.  For tiles sorted by length:
+  // half the XCDs then run long tiles (bound by the matrix cores) while the others run short ones
+  // (bound by the weight stream).
+  __device__ ItemMap(int n_tiles, int n_fb, bool both_ends = false) : ends(both_ends) {
     const int per_xcd = gridDim.x / kXcds;
     xcd = gridDim.x % kXcds == 0 && per_xcd > 0;
     fg = n_fb % 4 == 0 ? 4 : n_fb % 2 == 0 ? 2 : 1;
@@ -41,7 +44,9 @@ struct ItemMap {
 
   // Item of ticket t of queue q; false for the slots past the last tile of a partial chunk.
   __device__ bool item(int q, int t, int n_tiles, int& tile, int& fb) const {
-    const int chunk = q + t / (tg * fg) * nq;
+    int j = t / (tg * fg);
+    if (ends && (q & 1)) j = (n_chunks - 1 - q) / nq - j;
+    const int chunk = q + j * nq;
     const int local = t % (tg * fg);
     const int tgroup = chunk / n_fg;
     tile = tgroup * tg + local / fg;
