@@ -191,26 +191,34 @@ __device__ __forceinline__ uint4 lds_read16_r(const lds_u8* p) {
 
 // Many tokens: a block takes 128 tokens and all experts (NE blocks of 32, a quarter of them per
 // wave) for one K range of the split, so every token row is read once per split and every gate
-// row once per block.  The token rows of each 64-wide K step move into LDS once per block with
-// direct buffer -> LDS loads (two buffers: step st + 1 moves while step st is multiplied) and
-// are shared by the 4 waves; each wave streams its own gate rows into a ring of NB register
-// sets.  The k assignment is k_router_logits' (lane (r, h): row r, bytes [64 h, 64 h + 64) of
-// the step; MFMA i takes the i-th 16 bytes) for both operands, so no LDS transpose is needed.
-// The token stages are a ring of ND in LDS, moved ND - 1 steps ahead: the rows come from HBM
-// once, and one step of lead did not cover the miss latency.
-// In LDS a token row's 16-byte chunk j sits in slot j ^ (row & 7): the 8 lanes an LDS read
-// serves together hit distinct banks.  Per MFMA a wave reads 1 KB of LDS (one token
-// fragment) where holding the gate in LDS would cost one gate fragment per wave and token
-// block (twice the LDS traffic at E = 256).
-constexpr int kRouterStages = 4;  // token stages in LDS (16 KB each)
+// row once per block.  Both operands of each 64-wide K step move into LDS rings with direct
+// buffer -> LDS loads, whole 128-byte lines of 8 rows each, and are shared by the 4 waves.  Loaded
+// straight into MFMA operands, the gate took 16 bytes of 32 lines an instruction, and the address
+// path bounded the kernel (60 us at T = 8192, E = 256 for 12 us of MFMAs).  Waves 0 and 1 move the
+// tokens and waves 2 and 3 the gate: each wave counts its own moves, so the token moves (from HBM) run
+// further ahead than the gate's (from L2).
+// The k assignment is k_router_logits' (lane (r, h): row r, bytes [64 h, 64 h + 64) of the step;
+// MFMA i takes the i-th 16 bytes) for both operands.  In LDS a row's 16-byte chunk j sits in slot
+// j ^ (row / 2 & 7): the 16 rows of one read phase hit distinct banks.  Per step a wave reads 16 KB of
+// tokens and NE / 4 x 4 KB of gate for 4 NE MFMAs.
+template <int NE>
+struct RouterCfg {
+  static constexpr int TB = 4;                            // 32-token blocks per tile
+  static constexpr int NW = NE / 4;                       // 32-expert blocks per wave
+  static constexpr uint32_t kTokStage = TB * 32 * 128;    // 16 KB
+  static constexpr uint32_t kGateStage = NE * 32 * 128;   // 32 KB at E = 256
+  static constexpr int NG = NE <= 8 ? 3 : 2;              // stages of the gate ring
+  static constexpr int NT = NE <= 12 ? 4 : 2;             // stages of the token ring
+  static constexpr uint32_t kGateOff = NT * kTokStage;
+  static constexpr size_t kLds = kGateOff + NG * (size_t)kGateStage;
+  static_assert(NE % 4 == 0 && kLds <= 160 * 1024, "LDS of one CU");
+};
 
-template <int NE, int NB>
+template <int NE>
 __global__ __launch_bounds__(256) void k_router_logits_lds(LogitsArgs a) {
-  static_assert(NE % 4 == 0, "a quarter of the expert blocks per wave");
-  constexpr int NW = NE / 4;                 // 32-expert blocks per wave
-  constexpr int TB = 4;                      // 32-token blocks per block tile (128 tokens)
-  constexpr int ND = kRouterStages;
-  constexpr uint32_t kStage = TB * 32 * 128; // token bytes of one K step (16 KB)
+  using Cfg = RouterCfg<NE>;
+  constexpr int NW = Cfg::NW, TB = Cfg::TB, NT = Cfg::NT, NG = Cfg::NG;
+  constexpr int MT = TB * 32 / 8 / 2, MG = NE * 32 / 8 / 2;  // moves per step of a token / gate wave
   extern __shared__ __attribute__((aligned(1024))) uint8_t router_smem[];
   lds_u8* const lds = (lds_u8*)router_smem;
   pin(a.x);
@@ -231,26 +239,33 @@ __global__ __launch_bounds__(256) void k_router_logits_lds(LogitsArgs a) {
   const int t0 = tt * TB * 32;
   const int e0 = wave * NW * 32;
   const uint32_t row_bytes = (uint32_t)a.H * 2u;
-  const __amdgpu_buffer_rsrc_t rx = make_rsrc(a.x, (uint32_t)a.T * row_bytes);
-  const __amdgpu_buffer_rsrc_t rw = make_rsrc(a.wg, (uint32_t)a.E * row_bytes);
-  // Token rows this thread moves: row 32 p + tid / 8 of each pass p, into slot tid % 8 (a wave's
-  // move covers 8 whole rows, 1 KB of LDS in lane order), holding chunk slot ^ (row & 7).
-  uint32_t vx[TB];
-#pragma unroll
-  for (int p = 0; p < TB; ++p) {
-    const int row = 32 * p + (tid >> 3);
-    const uint32_t chunk = (uint32_t)((tid & 7) ^ (row & 7));
-    vx[p] = t0 + row < a.T ? (uint32_t)(t0 + row) * row_bytes + chunk * 16u : kOobOffset;
-  }
-  uint32_t vw[NW];
-#pragma unroll
-  for (int c = 0; c < NW; ++c) {
-    const int e = e0 + 32 * c + r;
-    vw[c] = e < a.E ? (uint32_t)e * row_bytes + 64u * h : kOobOffset;
-  }
-
   const int steps = a.H / kStepK;
-  const int st0 = (int)((int64_t)s * steps / a.S), st1 = (int)((int64_t)(s + 1) * steps / a.S);
+  const int st0 = (int)((int64_t)s * steps / a.S), n = (int)((int64_t)(s + 1) * steps / a.S) - st0;
+
+  // Rows this wave moves: 8 per move, lane l row l / 8 of them, the chunk that belongs in slot
+  // l % 8.  Rows past the last repeat it (their results are not stored).
+  const bool tok = wave < 2;
+  const int m0 = (wave & 1) * (tok ? MT : MG);  // first move
+  constexpr int MM = MT > MG ? MT : MG;
+  uint32_t vo[MM];
+#pragma unroll
+  for (int j = 0; j < MM; ++j) {
+    const int row = 8 * (m0 + j) + (lane >> 3);
+    const uint32_t chunk = (uint32_t)((lane & 7) ^ ((row >> 1) & 7));
+    vo[j] = (uint32_t)(tok ? min(t0 + row, a.T - 1) : min(row, a.E - 1)) * row_bytes + chunk * 16u;
+  }
+  const void* const src = tok ? (const void*)a.x : (const void*)a.wg;
+  const uint32_t src_bytes = (uint32_t)(tok ? a.T : a.E) * row_bytes;
+  // Move i of step j (relative to st0); steps past the last go through an empty resource, which reads
+  // no memory and keeps the counts of moves in flight.
+  auto move_src = [&](int j, __amdgpu_buffer_rsrc_t& rs, uint32_t& soff) __attribute__((always_inline)) {
+    rs = make_rsrc(src, j < n ? src_bytes : 0u);
+    soff = j < n ? (uint32_t)(st0 + j) * (kStepK * 2) : 0u;
+  };
+  // This wave's ring: NT stages of tokens or NG of gate rows.
+  const uint32_t ring0 = (tok ? 0u : Cfg::kGateOff) + (uint32_t)m0 * 1024u;
+  const uint32_t ring_stage = tok ? Cfg::kTokStage : Cfg::kGateStage;
+  const int ring_n = tok ? NT : NG;
 
   floatx16 acc[TB][NW];
 #pragma unroll
@@ -260,80 +275,118 @@ __global__ __launch_bounds__(256) void k_router_logits_lds(LogitsArgs a) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[tb][c][i] = 0.0f;
 
-  uint4 wr[NB][NW][4];
-  auto load_w = [&](int st, int slot) __attribute__((always_inline)) {
-    const uint32_t soff = (uint32_t)min(st, st1 - 1) * (kStepK * 2);
-#pragma unroll
-    for (int c = 0; c < NW; ++c)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) wr[slot][c][i] = buf_load<uint4, 0>(rw, vw[c] + 16u * i, soff);
+  // Step j: the moves of step j + NT - 1 (tokens) or j + NG - 1 (gate) into the buffer step j - 1 left,
+  // the MFMAs of step j with each 16-byte chunk's operands read during the MFMAs of the one before (the
+  // last chunk's MFMAs run in the next step), then a wait for this wave's moves of step j + 1 and its
+  // LDS reads, and the barrier that publishes step j + 1 and frees step j's buffers.  With one wave per
+  // SIMD nothing else fills the matrix cores while a wave issues moves and reads, so those are placed
+  // between the MFMAs, one or two behind each (issued ahead of them in one piece, a step took 2680
+  // cycles for 1024 of MFMAs).
+  auto wait_next = [&]() __attribute__((always_inline)) {
+    constexpr int VT = (NT - 2) * MT, VG = (NG - 2) * MG;
+    static_assert(VT < 64 && VG < 64, "counter range");
+    if (tok) wait_vmcnt<VT>();
+    else wait_vmcnt<VG>();
   };
-  auto move_x = [&](int st, int buf) __attribute__((always_inline)) {
-    const uint32_t soff = (uint32_t)min(st, st1 - 1) * (kStepK * 2);
-#pragma unroll
-    for (int p = 0; p < TB; ++p) lds_move16(rx, lds + buf * kStage + (32 * p + 8 * wave) * 128, vx[p], soff);
+  struct Ops {
+    uint4 v[TB + NW];
   };
-
-  // Step j issues the TB token moves of step j + ND - 1, then the 4 NW gate loads of step
-  // j + NB - 1 (steps past the last re-issue it, so the counts stay exact).  Waiting for all
-  // but the newest two steps' operations completes everything issued up to step j - 2, which
-  // holds step j's moves (issued at j - ND + 1) and gate loads (issued at j - NB + 1).
-  constexpr int kWait = 2 * (TB + 4 * NW);
-  static_assert(NB == 3 && ND >= NB && kWait < 64, "wait count");
-  auto step = [&](int st, auto u_c) __attribute__((always_inline)) {
-    constexpr int u = decltype(u_c)::value;
-    const int rel = st - st0;
-    __syncthreads();  // every wave is done with the stage step st + ND - 1 moves into
-    move_x(st + ND - 1, (rel + ND - 1) % ND);
-    load_w(st + NB - 1, (u + NB - 1) % NB);
-    wait_vmcnt<kWait>();
-    __syncthreads();  // ... and every wave's moves of step st have landed
-    const lds_u8* cur = lds + (rel % ND) * kStage;
+  constexpr int NM = TB * NW, NR = TB + NW;  // MFMAs and reads of one chunk
+  const uint32_t lx = (uint32_t)r * 128u, lsw = (uint32_t)((r >> 1) & 7);
+  auto read1 = [&](const lds_u8* tc, const lds_u8* gc, int i, int k, Ops& o) __attribute__((always_inline)) {
+    const uint32_t off = lx + (((4u * h + i) ^ lsw) << 4);
+    o.v[k] = k < TB ? lds_read16_r(tc + off + k * 4096) : lds_read16_r(gc + off + (e0 + 32 * (k - TB)) * 128);
+  };
+  auto mul1 = [&](const Ops& o, int m) __attribute__((always_inline)) {
+    const int tb = m / NW, c = m % NW;
+    acc[tb][c] = mfma32x32x16(o.v[tb], o.v[TB + c], acc[tb][c]);
+  };
+  Ops A, B;
+  int dst_i = ring_n - 1, t_i = 0, g_i = 0;  // ring slots of the moves' and the reads' buffers
+  auto step = [&](lds_u8* __restrict__ dst, const lds_u8* __restrict__ tc, const lds_u8* __restrict__ gc, int j)
+      __attribute__((always_inline)) {
+    __amdgpu_buffer_rsrc_t rs;
+    uint32_t soff;
+    move_src(j + ring_n - 1, rs, soff);
+    // Chunk 0's reads and the moves, between the last chunk's MFMAs of the step before.
+    constexpr int MVS = (MM + NM - 1) / NM;  // moves behind each of them
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const uint32_t off = (uint32_t)r * 128u + (uint32_t)(((4 * h + i) ^ (r & 7)) * 16);
+    for (int k = 0; k < NR; ++k) read1(tc, gc, 0, k, A);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int tb = 0; tb < TB; ++tb) {
-        const uint4 xf = lds_read16_r(cur + tb * 32 * 128 + off);
+    for (int m = 0; m < NM; ++m) {
+      if (j > 0) mul1(B, m);
 #pragma unroll
-        for (int c = 0; c < NW; ++c) acc[tb][c] = mfma32x32x16(xf, wr[u][c][i], acc[tb][c]);
+      for (int i = m * MVS; i < (m + 1) * MVS; ++i)
+        if (i < MT || (i < MG && !tok)) lds_move16(rs, dst + i * 1024, vo[i], soff);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int i = 1; i < 4; ++i) {
+      Ops& cur = i % 2 ? A : B;
+      Ops& nxt = i % 2 ? B : A;
+#pragma unroll
+      for (int m = 0; m < NM; ++m) {
+        mul1(cur, m);
+#pragma unroll
+        for (int k = 0; k < NR; ++k)
+          if (k * NM / NR == m) read1(tc, gc, i, k, nxt);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
+    wait_next();
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
   };
-  if (st0 < st1) {  // the plan gives every split a step; st0 and st1 are uniform over the block
-    // The same issue order as the steps: moves of step d, then the gate loads of step d.
+#pragma unroll 1
+  for (int j = 0; j < ring_n - 1; ++j) {
+    __amdgpu_buffer_rsrc_t rs;
+    uint32_t soff;
+    move_src(j, rs, soff);
 #pragma unroll
-    for (int d = 0; d < ND - 1; ++d) {
-      move_x(st0 + d, d);
-      if (d < NB - 1) load_w(st0 + d, d);
-    }
-    int st = st0;
-    for (; st + NB <= st1; st += NB) {
-      step(st, std::integral_constant<int, 0>{});
-      step(st + 1, std::integral_constant<int, 1>{});
-      step(st + 2, std::integral_constant<int, 2>{});
-    }
-    if (st < st1) step(st, std::integral_constant<int, 0>{});
-    if (st + 1 < st1) step(st + 1, std::integral_constant<int, 1>{});
-    // The last steps' moves and loads re-read the last step: drain them (moves into LDS must
-    // land before the workgroup ends).
-    wait_vmcnt<0>();
+    for (int i = 0; i < MM; ++i)
+      if (i < MT || (i < MG && !tok)) lds_move16(rs, lds + ring0 + j * ring_stage + i * 1024, vo[i], soff);
   }
+  wait_next();
+  __syncthreads();
+  for (int j = 0; j < n; ++j) {
+    step(lds + ring0 + dst_i * ring_stage, lds + t_i * Cfg::kTokStage, lds + Cfg::kGateOff + g_i * Cfg::kGateStage, j);
+    dst_i = dst_i + 1 == ring_n ? 0 : dst_i + 1;
+    t_i = t_i + 1 == NT ? 0 : t_i + 1;
+    g_i = g_i + 1 == NG ? 0 : g_i + 1;
+  }
+#pragma unroll
+  for (int m = 0; m < NM; ++m) mul1(B, m);
+  wait_vmcnt<0>();  // empty moves write LDS too: they must land before the workgroup ends
 
   // Accumulator register q of block (tb, c): token 32 tb + 8 (q / 4) + 4 h + q % 4, expert
-  // e0 + 32 c + r.
-  float* out = a.part + (size_t)s * a.T * a.E;
+  // e0 + 32 c + r.  The code runs once per wave, so its time is the instruction fetch: whole tiles
+  // store with one scalar offset a row and no row check.
+  float* out = a.part + ((size_t)s * a.T + t0) * a.E;
+  const int rows = min(a.T - t0, TB * 32);
+  const __amdgpu_buffer_rsrc_t ro = make_rsrc(out, (uint32_t)rows * (uint32_t)a.E * 4u);
 #pragma unroll
-  for (int tb = 0; tb < TB; ++tb)
+  for (int c = 0; c < NW; ++c) {
+    const int e = e0 + 32 * c + r;
+    const uint32_t vo = e < a.E ? (uint32_t)(4 * h * a.E + e) * 4u : kOobOffset;
+    if (rows == TB * 32) {
 #pragma unroll
-    for (int c = 0; c < NW; ++c) {
-      const int e = e0 + 32 * c + r;
+      for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-      for (int q = 0; q < 16; ++q) {
-        const int t = t0 + 32 * tb + 8 * (q >> 2) + 4 * h + (q & 3);
-        if (t < a.T && e < a.E) out[(size_t)t * a.E + e] = acc[tb][c][q];
-      }
+        for (int q = 0; q < 16; ++q)
+          __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(acc[tb][c][q]), ro, vo,
+                                                (uint32_t)(32 * tb + 8 * (q >> 2) + (q & 3)) * (uint32_t)a.E * 4u, 0);
+    } else {
+#pragma unroll
+      for (int tb = 0; tb < TB; ++tb)
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int t = 32 * tb + 8 * (q >> 2) + 4 * h + (q & 3);
+          if (t < rows && e < a.E) out[(size_t)t * a.E + e] = acc[tb][c][q];
+        }
     }
+  }
 }
 
 // Order-preserving key of a float: larger float -> larger unsigned key; -0 is taken as +0.
@@ -366,45 +419,58 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 }
 
 // Top-k selection and gates of token t from the E logits the wave holds (expert lane + 64 j
-// in v[j], bit j of `left` set where that expert exists).  Each round takes the largest key
-// left; among lanes and registers holding it the lowest expert id wins (smallest j, then
-// lowest lane, found with ballots).  The rounds are a loop, not unrolled: the kernel stays
-// small, so a block's first instruction fetches are few.
+// in v[j], bit j of `left` set where that expert exists).  Each lane first sorts its experts, by
+// falling key and rising id, so a round looks at one value a lane: the wave's largest key wins, among
+// equal keys the lowest expert id, and the winner's lane moves its list up.  (Scanning every lane's
+// values each round took 700 VALU instructions a token, and at T = 8192 bounded the kernel.)  The
+// rounds are a loop, not unrolled: the kernel stays small, so a block's first instruction fetches
+// are few.
 template <int NJ>
 __device__ __forceinline__ void select_topk(const float (&v)[NJ], uint32_t left, int lane, int t,
                                             const TopkArgs& a) {
-  uint32_t key[NJ];
+  // Key in the high word, the id's complement in the low word; 0 where there is no expert (a NaN's
+  // key may be 0, its low word is not).
+  uint64_t c[NJ];
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) key[j] = float_key(v[j]);
+  for (int j = 0; j < NJ; ++j)
+    c[j] = ((left >> j) & 1u) ? (uint64_t)float_key(v[j]) << 32 | (uint32_t)~(kWave * j + lane) : 0ull;
+  // Odd-even transposition sort, falling.
+#pragma unroll
+  for (int p = 0; p < NJ; ++p)
+#pragma unroll
+    for (int j = p & 1; j + 1 < NJ; j += 2) {
+      const bool sw = c[j + 1] > c[j];
+      const uint64_t x = sw ? c[j + 1] : c[j], y = sw ? c[j] : c[j + 1];
+      c[j] = x;
+      c[j + 1] = y;
+    }
   int32_t my_id = 0;
-  float my_val = 0.0f, top = 0.0f, z = 0.0f;
+  uint32_t my_key = 0;
 #pragma unroll 1
   for (int r = 0; r < a.k; ++r) {
-    uint32_t m = 0;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      if ((left >> j) & 1u) m = max(m, key[j]);
-    m = wave_max_u32(m);
-    int32_t e = -1;
-#pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      if (e < 0) {
-        const uint64_t hold = __ballot(((left >> j) & 1u) && key[j] == m);
-        if (hold) e = kWave * j + (int32_t)__builtin_ctzll(hold);
-      }
+    const uint32_t key = (uint32_t)(c[0] >> 32), low = (uint32_t)c[0];
+    const uint32_t m = wave_max_u32(key);
+    const uint64_t hold = __ballot(key == m);
+    uint32_t win = (uint32_t)__builtin_amdgcn_readlane((int)low, (int)__builtin_ctzll(hold));
+    if (m == 0 || (hold & (hold - 1)) != 0) win = wave_max_u32(key == m ? low : 0u);  // ties
+    if (lane == r) {
+      my_id = (int32_t)~win;
+      my_key = m;
     }
-    if ((e & (kWave - 1)) == lane) left &= ~(1u << (e / kWave));
-    const float val = key_float(m);
-    if (r == 0) top = val;
-    z += expf(val - top);
-    if (r == lane) {
-      my_id = e;
-      my_val = val;
+    if (low == win && key == m) {
+#pragma unroll
+      for (int j = 0; j + 1 < NJ; ++j) c[j] = c[j + 1];
+      c[NJ - 1] = 0ull;
     }
   }
+  const float top = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, key_float(my_key)), 0));
+  const float ex = expf(key_float(my_key) - top);
+  float z = 0.0f;
+  for (int r = 0; r < a.k; ++r)
+    z += __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, ex), r));
   if (lane < a.k) {
     a.ids[(size_t)t * a.k + lane] = my_id;
-    a.w[(size_t)t * a.k + lane] = expf(my_val - top) / z;
+    a.w[(size_t)t * a.k + lane] = ex / z;
   }
 }
 
@@ -412,6 +478,15 @@ __device__ __forceinline__ void select_topk(const float (&v)[NJ], uint32_t left,
 // NJ = 64-expert groups held per lane (ceil(E / 64) rounded up to a power of two).
 template <int NJ>
 __global__ __launch_bounds__(256) void k_router_topk_wave(TopkArgs a) {
+  pin(a.part);
+  pin(a.bias);
+  pin(a.logits);
+  pin(a.ids);
+  pin(a.w);
+  pin(a.T);
+  pin(a.E);
+  pin(a.k);
+  pin(a.S);
   const int lane = threadIdx.x & 63;
   const int t = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (t >= a.T) return;
@@ -424,11 +499,20 @@ __global__ __launch_bounds__(256) void k_router_topk_wave(TopkArgs a) {
   }
   const float* p = a.part + (size_t)t * a.E + lane;
   const size_t split = (size_t)a.T * a.E;
+  // Four splits' loads in flight at a time, added in split order.
 #pragma unroll 1
-  for (int s = 0; s < a.S; ++s) {
+  for (int s0 = 0; s0 < a.S; s0 += 4) {
+    float q[4][NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j)
-      if ((left >> j) & 1u) v[j] += p[(size_t)s * split + kWave * j];
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        q[u][j] = (s0 + u < a.S && ((left >> j) & 1u)) ? p[(size_t)(s0 + u) * split + kWave * j] : 0.0f;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if (s0 + u < a.S) v[j] += q[u][j];
   }
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
@@ -442,13 +526,22 @@ __global__ __launch_bounds__(256) void k_router_topk_wave(TopkArgs a) {
 }
 
 // Many splits (few tokens): a block per token.  Each thread sums MB = NJ / 4 experts over the
-// S partials in split order, 32 / MB splits' loads in flight at a time (the whole sum in one
-// round trip for S <= 32 at E <= 256); the logits meet in LDS and the first wave selects.
+// S partials in split order, B splits' loads in flight at a time (the whole sum in one
+// round trip for S <= 32 at E <= 512); the logits meet in LDS and the first wave selects.
 template <int NJ>
 __global__ __launch_bounds__(256) void k_router_topk_block(TopkArgs a) {
   constexpr int MB = NJ >= 4 ? NJ / 4 : 1;
-  constexpr int B = 32 / MB;
+  constexpr int B = MB == 1 ? 32 : 64 / MB;
   __shared__ float lg[NJ * kWave];
+  pin(a.part);
+  pin(a.bias);
+  pin(a.logits);
+  pin(a.ids);
+  pin(a.w);
+  pin(a.T);
+  pin(a.E);
+  pin(a.k);
+  pin(a.S);
   const int t = blockIdx.x;
   const float* p = a.part + (size_t)t * a.E + threadIdx.x;
   const size_t split = (size_t)a.T * a.E;
@@ -590,12 +683,11 @@ damoe_status damoe_router(const uint16_t* x, const uint16_t* wg, const float* bi
   LogitsArgs la{x, wg, static_cast<float*>(ws), T, H, E, p.S, p.tiles_t, p.tiles_e, p.n_items, p.per_xcd};
   const dim3 grid(8 * p.per_xcd);
   if (p.ne > 0) {
-    const size_t lds = (size_t)kRouterStages * 4 * 32 * 128;  // 128-token x 64-k stages
     switch (p.ne) {
-      case 4: hipLaunchKernelGGL((k_router_logits_lds<4, 3>), grid, dim3(256), lds, stream, la); break;
-      case 8: hipLaunchKernelGGL((k_router_logits_lds<8, 3>), grid, dim3(256), lds, stream, la); break;
-      case 12: hipLaunchKernelGGL((k_router_logits_lds<12, 3>), grid, dim3(256), lds, stream, la); break;
-      default: hipLaunchKernelGGL((k_router_logits_lds<16, 3>), grid, dim3(256), lds, stream, la); break;
+      case 4: hipLaunchKernelGGL(k_router_logits_lds<4>, grid, dim3(256), RouterCfg<4>::kLds, stream, la); break;
+      case 8: hipLaunchKernelGGL(k_router_logits_lds<8>, grid, dim3(256), RouterCfg<8>::kLds, stream, la); break;
+      case 12: hipLaunchKernelGGL(k_router_logits_lds<12>, grid, dim3(256), RouterCfg<12>::kLds, stream, la); break;
+      default: hipLaunchKernelGGL(k_router_logits_lds<16>, grid, dim3(256), RouterCfg<16>::kLds, stream, la); break;
     }
   } else if (p.wt == 4) {
     hipLaunchKernelGGL((k_router_logits<4, 2, 3>), grid, dim3(512), 0, stream, la);
@@ -622,12 +714,16 @@ namespace damoe {
 
 // Dynamic LDS above 64 KB needs the per-kernel limit (set once per device).
 hipError_t router_set_lds_limits() {
-  const void* fns[] = {reinterpret_cast<const void*>(&k_router_logits_lds<4, 3>),
-                       reinterpret_cast<const void*>(&k_router_logits_lds<8, 3>),
-                       reinterpret_cast<const void*>(&k_router_logits_lds<12, 3>),
-                       reinterpret_cast<const void*>(&k_router_logits_lds<16, 3>)};
-  for (const void* f : fns) {
-    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, kRouterStages * 4 * 32 * 128);
+  struct Fn {
+    const void* f;
+    size_t lds;
+  };
+  const Fn fns[] = {{reinterpret_cast<const void*>(&k_router_logits_lds<4>), RouterCfg<4>::kLds},
+                    {reinterpret_cast<const void*>(&k_router_logits_lds<8>), RouterCfg<8>::kLds},
+                    {reinterpret_cast<const void*>(&k_router_logits_lds<12>), RouterCfg<12>::kLds},
+                    {reinterpret_cast<const void*>(&k_router_logits_lds<16>), RouterCfg<16>::kLds}};
+  for (const Fn& f : fns) {
+    const hipError_t e = hipFuncSetAttribute(f.f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.lds);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
