@@ -217,14 +217,18 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     }
     // Moves of stages past the last go through an empty resource: they read no memory, and the
     // counts of moves in flight stay the same.
-    auto dma_tok = [&](int st, lds_t* sb) __attribute__((always_inline)) {
+    auto tok_src = [&](int st, uint32_t& soff) __attribute__((always_inline)) {
       const bool in = st < nst;
       const uint32_t s0 = in ? st : 0;
-      const __amdgpu_buffer_rsrc_t rx =
-          GLU ? make_rsrc(a->x, in ? xbytes : 0u)
-              : make_rsrc(a->x + ((size_t)s0 * A + p0) * BK, in ? (uint32_t)rows * (BK * 2u) : 0u);
+      soff = GLU ? s0 * (BK * 2u) : 0u;
+      return GLU ? make_rsrc(a->x, in ? xbytes : 0u)
+                 : make_rsrc(a->x + ((size_t)s0 * A + p0) * BK, in ? (uint32_t)rows * (BK * 2u) : 0u);
+    };
+    auto dma_tok = [&](int st, lds_t* sb) __attribute__((always_inline)) {
+      uint32_t soff;
+      const __amdgpu_buffer_rsrc_t rx = tok_src(st, soff);
 #pragma unroll
-      for (int j = 0; j < NTOK; ++j) dma16(rx, sb + (NTOK * wave + j) * kMove, xo[j], GLU ? s0 * (BK * 2u) : 0u);
+      for (int j = 0; j < NTOK; ++j) dma16(rx, sb + (NTOK * wave + j) * kMove, xo[j], soff);
     };
 
     // Weight operand of this wave: 32 rows, lane l row l % 32, 8 columns 8 (l / 32) .. of a
@@ -283,29 +287,26 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     // 2 ks + l / 32 of the stage, at its swizzled slot.  Set s of a stage is k-step s / NH, token
     // blocks 4 (s % NH) .. of it.
     uint4 tf[2][NB];
-    auto read_set = [&](int s, const lds_t* tcur, uint4 (&o)[NB]) __attribute__((always_inline)) {
+    auto read1 = [&](int s, const lds_t* tcur, int i, uint4 (&o)[NB]) __attribute__((always_inline)) {
       const int ks = s / NH, n0 = 4 * (s % NH);
       const lds_t* row = tcur + l32 * 128 + (((2 * ks + lh) ^ ((l32 >> 1) & 7)) << 4);
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-        if (n0 + i < NN) o[i] = lds_read16(row + (n0 + i) * 4096);
+      if (i < NB && n0 + i < NN) o[i] = lds_read16(row + (n0 + i) * 4096);
     };
     uint4 wv[kBigMB];
     float sc = 0.f;
-    auto mma_set = [&](int s, int d, const uint4 (&o)[NB]) __attribute__((always_inline)) {
-      const int ks = s / NH, n0 = 4 * (s % NH);
-      if (n0 == 0) {
+    auto conv = [&](int s, int d) __attribute__((always_inline)) {
+      if (s % NH == 0) {
 #pragma unroll
         for (int m = 0; m < kBigMB; ++m) {
-          if constexpr (FP8) wv[m] = fp8x8_to_bf16x8(wf[d][ks][m], sc);
-          else wv[m] = wf[d][ks][m];
+          if constexpr (FP8) wv[m] = fp8x8_to_bf16x8(wf[d][s / NH][m], sc);
+          else wv[m] = wf[d][s / NH][m];
         }
       }
-#pragma unroll
-      for (int i = 0; i < NB; ++i)
-        if (n0 + i < NN)
-#pragma unroll
-          for (int m = 0; m < kBigMB; ++m) acc[m][n0 + i] = mfma32x32x16(wv[m], o[i], acc[m][n0 + i]);
+    };
+    constexpr int NMF = NB * kBigMB;  // MFMAs of a set (fewer in a last half set)
+    auto mma1 = [&](int s, int i, const uint4 (&o)[NB]) __attribute__((always_inline)) {
+      const int n = 4 * (s % NH) + i / kBigMB, m = i % kBigMB;
+      if (n < NN) acc[m][n] = mfma32x32x16(wv[m], o[i / kBigMB], acc[m][n]);
     };
 
     // Software pipeline.  Iteration t (between barriers t - 1 and t): the DMA of the tokens of
@@ -324,21 +325,33 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     auto iter = [&](lds_t* __restrict__ tdst, const lds_t* __restrict__ tcur, int t, auto d_c)
         __attribute__((always_inline)) {
       constexpr int d = decltype(d_c)::value, dp = (d + D - 1) % D;
-      dma_tok(t + NT - 1, tdst);
+      uint32_t soff;
+      const __amdgpu_buffer_rsrc_t rx = tok_src(t + NT - 1, soff);
       float sc_next = 0.f;
       if constexpr (FP8) sc_next = sc_lane[(t * BK) >> 7];
+      // Behind each MFMA of the set before: one operand read of this set, or moves of the stage ahead.
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
-        read_set(s, tcur, tf[s & 1]);
-        __builtin_amdgcn_sched_barrier(0);
+        const int sp = s == 0 ? NS - 1 : s - 1;
+        constexpr int MV = (NTOK + NMF - 1) / NMF;
+        conv(sp, s == 0 ? dp : d);  // (of nothing in iteration 0)
+#pragma unroll
+        for (int i = 0; i < NMF; ++i) {
+          if (s > 0 || t > 0) mma1(sp, i, tf[sp & 1]);
+          read1(s, tcur, i, tf[s & 1]);
+          if (s == 0) {
+#pragma unroll
+            for (int j = i * MV; j < (i + 1) * MV; ++j)
+              if (j < NTOK) dma16(rx, tdst + (NTOK * wave + j) * kMove, xo[j], soff);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
         if (s == 0) {
-          if (t > 0) mma_set(NS - 1, dp, tf[1]);
           wload(dp, 3);
           wstage(t + D);
           sc = sc_next;
-        } else {
-          mma_set(s - 1, d, tf[(s - 1) & 1]);
-          if (s % NH == 0) wload(d, s / NH - 1);
+        } else if (s % NH == 0) {
+          wload(d, s / NH - 1);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -382,10 +395,12 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     while (t + D <= nst) trip(std::integral_constant<int, D>{});
     if (D == 4 && !FP8 && t < nst) {
       trip(std::integral_constant<int, 2>{});
-      mma_set(NS - 1, 1, tf[1]);
+      conv(NS - 1, 1);
     } else {
-      mma_set(NS - 1, D - 1, tf[1]);
+      conv(NS - 1, D - 1);
     }
+#pragma unroll
+    for (int i = 0; i < NMF; ++i) mma1(NS - 1, i, tf[1]);
     // Moves and loads past the last stage may still be in flight: drain before the next item's.
     wait_cnt<0, 0>();
     __syncthreads();
