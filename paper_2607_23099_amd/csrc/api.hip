@@ -419,7 +419,8 @@ static damoe_status fused_impl(const damoe_layer* L, int32_t stage_mask, const u
   // Kernel classes to launch: the forced variant's, else every class holding a candidate.  The
   // launches of a class whose variant the device did not choose return at once.
   const uint32_t big_bit = 1u << kBigVariant, big8_bit = 1u << kBig8Variant;
-  // The big-tile kernel runs GEMM1 of both big-tile variants.
+  // The big-tile kernel runs GEMM1 of both big-tile variants and, with fp8 weights, of both deep-ring
+  // variants.
   const bool big = force_variant >= 0 ? force_variant == kBigVariant : (candidates & big_bit) != 0;
   const bool big8 = force_variant >= 0 ? force_variant == kBig8Variant : (candidates & big8_bit) != 0;
   const uint32_t deep_bit = 1u << kDeepVariant, deep8_bit = 1u << kDeep8Variant;
@@ -435,8 +436,8 @@ static damoe_status fused_impl(const damoe_layer* L, int32_t stage_mask, const u
   if ((big8 || deep8) && (size_t)T * L->k * L->I >= ((size_t)1 << 31)) return DAMOE_ERR_UNSUPPORTED;
   if (stage_mask & 1) {
     if (mega && launch_gemm1(g1, dev->cus, stream) != hipSuccess) return DAMOE_ERR_HIP;
-    if ((deep || deep8) && launch_deep_gemm1(g1, dev->cus, stream) != hipSuccess) return DAMOE_ERR_HIP;
-    if ((big || big8) && launch_big_gemm1(g1, dev->cus, stream) != hipSuccess) return DAMOE_ERR_HIP;
+    if (deep && !g1.fp8 && launch_deep_gemm1(g1, dev->cus, stream) != hipSuccess) return DAMOE_ERR_HIP;
+    if ((big || big8 || ((deep || deep8) && g1.fp8)) && launch_big_gemm1(g1, dev->cus, stream) != hipSuccess) return DAMOE_ERR_HIP;
   }
   if (stage_mask & 2) {
     if (mega && launch_gemm2(g2, dev->cus, stream) != hipSuccess) return DAMOE_ERR_HIP;

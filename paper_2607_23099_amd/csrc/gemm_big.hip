@@ -143,8 +143,9 @@ __device__ __forceinline__ args_ptr item_args() {
 // variants, then quantised to e4m3 with one E8M0 scale per 32 features of a row, into out
 // (codes [N / 64][A][64]) and o8s (scale words [N / 64][A][4]), the operand of its fp8-MFMA
 // GEMM2, stored stage-major so that each of GEMM2's moves reads contiguous bytes.
+// rowmajor_h: bf16 h as [A][N], for the deep-ring variant's GEMM2 (fp8 weights).
 template <bool GLU, bool FP8, bool PK>
-__device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx) {
+__device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx, bool rowmajor_h) {
   constexpr int FEAT = GLU ? kBigRows / 2 : kBigRows;  // output features per item
   constexpr int EB = FP8 ? 1 : 2;
   constexpr int BK = kBigBK;
@@ -412,6 +413,8 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     const args_ptr ae = item_args();
     const int Ne = ae->N, Ae = ae->A;
     void* const out = ae->out;
+    // h: bytes from one position to the next, and from one 64-feature stage to the next.
+    const size_t h_row = rowmajor_h ? (size_t)Ne * 2 : BK * 2, h_stage = rowmajor_h ? BK * 2 : (size_t)Ae * BK * 2;
     auto swap = [&](uint32_t& x, uint32_t& y) __attribute__((always_inline)) {
       const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
       x = r[0];
@@ -471,8 +474,8 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
           swap(pk.x, pk.z);
           swap(pk.y, pk.w);
           if (i < rows)
-            *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(out) +
-                                      ((size_t)(f0 / BK) * Ae + (p0 + i)) * BK + f0 % BK + 16 * m + 8 * lh) = pk;
+            *reinterpret_cast<uint4*>(reinterpret_cast<uint8_t*>(out) + (size_t)(f0 / BK) * h_stage +
+                                      (size_t)(p0 + i) * h_row + (f0 % BK + 16 * m + 8 * lh) * 2) = pk;
         }
       }
     } else {
@@ -524,10 +527,14 @@ __global__ void __launch_bounds__(kBigThreads, 1) k_gemm_big(GemmArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&a.ctrl[0], DAMOE_DEVERR_VARIANT);
     return;
   }
-  // This kernel runs the big-tile variant, and GEMM1 of the fp8-MFMA variant (fp8 weights).
-  const bool mx = GLU && FP8 && v == kBig8Variant;
-  if (v != kBigVariant && !mx) return;  // the device chose a variant of another kernel class
-  big_body<GLU, FP8, PK>(a, (lds_t*)big_smem, mx);
+  // This kernel runs the big-tile variant and, with fp8 weights, GEMM1 of both fp8-MFMA variants and
+  // of the deep-ring variant.  The deep-ring kernel's own fp8 GEMM1 decoded each weight operand for
+  // tiles of 64 tokens and padded them to 16: DeepSeek-V3 shape, T = 1024, alpha = 1, 1626 us against
+  // 1440 us here; at 64 tokens an expert, its best case, 1557 against 1577 us.
+  const bool mx = GLU && FP8 && (v == kBig8Variant || v == kDeep8Variant);
+  const bool rowmajor_h = GLU && FP8 && v == kDeepVariant;
+  if (v != kBigVariant && !mx && !rowmajor_h) return;  // the device chose another kernel class
+  big_body<GLU, FP8, PK>(a, (lds_t*)big_smem, mx, rowmajor_h);
 }
 
 template <bool GLU>

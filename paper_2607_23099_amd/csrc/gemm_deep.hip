@@ -2,8 +2,9 @@
 // few dozen tokens each: prefill over many experts, or skewed mid-size decode batches.  Such a
 // call is bound by the weight stream, and the other classes lose there in two ways: a stream
 // item moves as many token bytes as weight bytes (its 4 waves split K, so every feature block
-// re-reads the tile's token rows), and a big-tile item moves its 256 weight rows through an LDS
-// ring only two stages deep, so its short tiles wait on memory latency.
+// re-reads the tile's token rows), and a big-tile item moves its token rows once per 256 weight
+// rows instead of 512.  fp8 weights take this kernel for GEMM2 only: their GEMM1 is the big-tile
+// kernel's.
 //
 // One workgroup of 8 waves per CU.  A work item is (tile of up to 64 tokens of one expert,
 // 512 weight rows): for GEMM1 the rows are 256 features of W1 (gate) and the same 256 of W3
@@ -37,12 +38,10 @@ constexpr uint32_t kDeepStage = (uint32_t)kDeepBM * kDeepBK * 2;   // 16 KB of t
 constexpr size_t kDeepLds = 2 * (size_t)kDeepStage + 16;           // two stages + ticket word
 static_assert(kDeepBM == 16 << kDeepTileClass, "tile list of the class");
 
-// mx: GEMM1 of the fp8-MFMA deep-ring variant (fp8 weights only): h is rounded to bf16 as for
-// the other variants, then quantised to e4m3 with one E8M0 scale per 32 features of a row into
-// out (codes [N / 64][A][64]) and o8s (scale words [N / 64][A][4]), the stage-major operand of
-// the fp8-MFMA GEMM2 (the layout the big-tile kernel writes for it).
+// GEMM1 (GLU) takes bf16 weights only: with fp8 weights the big-tile kernel runs it.
 template <bool GLU, bool FP8, bool PK>
-__device__ __forceinline__ void deep_body(const GemmArgs& a, uint8_t* __restrict__ lds, bool mx) {
+__device__ __forceinline__ void deep_body(const GemmArgs& a, uint8_t* __restrict__ lds) {
+  static_assert(!(GLU && FP8), "GEMM1 of fp8 weights runs on the big-tile kernel");
   constexpr int BM = kDeepBM, NRW = kDeepNRW, NX = BM / 16, D = deep_ring<FP8>();
   // Stages per loop iteration: the ring slot of k-step ks is ks % D, a constant in the body.
   constexpr int G = D / (D % 4 == 0 ? 4 : D % 2 == 0 ? 2 : 1);  // 4 G = lcm(4, D) k-steps
@@ -120,9 +119,9 @@ __device__ __forceinline__ void deep_body(const GemmArgs& a, uint8_t* __restrict
       if (PK) wo[b] = ((uint32_t)(f0 / 16) * (uint32_t)(K / 32) * 64u + lane) * 8u * EB;
       else wo[b] = ((uint32_t)(f0 + rl) * (uint32_t)K + gl * 8) * EB;
     }
-    // fp8 block scales of the wave's rows (one 128-row block per matrix): lane l holds the
+    // fp8 block scales of the wave's rows (one 128-row block): lane l holds the
     // scales of 128-column blocks l and l + 64, k-step ks reads block ks / 4 with a lane read.
-    float sg[2] = {0.f, 0.f}, su[2] = {0.f, 0.f};
+    float sg[2] = {0.f, 0.f};
     if constexpr (FP8) {
       const int sk = K / 128, srow = w0 / 128;
       if (srow < N / 128) {
@@ -130,10 +129,7 @@ __device__ __forceinline__ void deep_body(const GemmArgs& a, uint8_t* __restrict
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           const int kb = lane + 64 * h;
-          if (kb < sk) {
-            sg[h] = a.sa[sbase + kb];
-            if (GLU) su[h] = a.sb[sbase + kb];
-          }
+          if (kb < sk) sg[h] = a.sa[sbase + kb];
         }
       }
     }
@@ -193,11 +189,8 @@ __device__ __forceinline__ void deep_body(const GemmArgs& a, uint8_t* __restrict
           const int sel = kb >> 6, ln = kb & 63;
           const float s_g = __builtin_bit_cast(float, __builtin_amdgcn_readlane(
                                 __builtin_bit_cast(int, sel ? sg[1] : sg[0]), ln));
-          const float s_u = GLU ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(
-                                      __builtin_bit_cast(int, sel ? su[1] : su[0]), ln))
-                                : s_g;
 #pragma unroll
-          for (int b = 0; b < NRW; ++b) wv[b] = fp8x8_to_bf16x8(wf[(RS + kk) % D][b], (GLU && b >= 2) ? s_u : s_g);
+          for (int b = 0; b < NRW; ++b) wv[b] = fp8x8_to_bf16x8(wf[(RS + kk) % D][b], s_g);
         } else {
 #pragma unroll
           for (int b = 0; b < NRW; ++b) wv[b] = wf[(RS + kk) % D][b];
@@ -250,37 +243,6 @@ __device__ __forceinline__ void deep_body(const GemmArgs& a, uint8_t* __restrict
 #pragma unroll
     for (int s = 0; s < NX; ++s) {
       const int i = s * 16 + rl;
-      if constexpr (GLU && FP8) {
-        if (mx) {
-          // The wave's 32 features w0 .. w0 + 31 of token i (a 32-aligned MX block): lane l holds
-          // 4 of each 16-feature half, so the block maximum is a max over the 4 lanes l % 16 +
-          // 16 j, taken before the row check (those lanes share the token).
-          float hb[2][4];
-          float amax = 0.f;
-#pragma unroll
-          for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const float g = acc[b][s][r], u = acc[b + 2][s][r];
-              hb[b][r] = (float)(__bf16)(g / (1.0f + __expf(-g)) * u);
-              amax = fmaxf(amax, fabsf(hb[b][r]));
-            }
-          amax = fmaxf(amax, __shfl_xor(amax, 16));
-          amax = fmaxf(amax, __shfl_xor(amax, 32));
-          const uint32_t sc = mx_scale_byte(amax);
-          const float inv = mx_inv_scale(sc);
-          if (i < rows && w0 < N) {
-            const size_t srow = (size_t)(w0 / 64) * a.A + (p0 + i);
-            uint8_t* h8 = reinterpret_cast<uint8_t*>(a.out) + srow * 64 + w0 % 64;
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-              *reinterpret_cast<uint32_t*>(h8 + 16 * b + 4 * gl) =
-                  e4m3x4(hb[b][0] * inv, hb[b][1] * inv, hb[b][2] * inv, hb[b][3] * inv);
-            if (gl == 0) a.o8s[srow * 4 + (w0 / 32) % 2] = (uint8_t)sc;
-          }
-          continue;
-        }
-      }
       if (i >= rows) continue;
       uint16_t* orow = reinterpret_cast<uint16_t*>(a.out) + (size_t)(p0 + i) * N;
       if (GLU) {
@@ -330,32 +292,25 @@ __global__ void __launch_bounds__(kDeepThreads, 1) k_gemm_deep(GemmArgs a) {
     if (blockIdx.x == 0 && threadIdx.x == 0) atomicOr(&a.ctrl[0], DAMOE_DEVERR_VARIANT);
     return;
   }
-  // This kernel runs the deep-ring variant, and GEMM1 of the fp8-MFMA deep-ring variant.
-  const bool mx = GLU && FP8 && v == kDeep8Variant;
-  if (v != kDeepVariant && !mx) return;  // the device chose a variant of another kernel class
-  deep_body<GLU, FP8, PK>(a, deep_smem, mx);
+  if (v != kDeepVariant) return;  // the device chose a variant of another kernel class
+  deep_body<GLU, FP8, PK>(a, deep_smem);
 }
 
-template <bool GLU>
+template <bool GLU, bool FP8>
 hipError_t launch_deep_stage(const GemmArgs& a, int grid, hipStream_t stream) {
-  if (a.fp8) {
-    if (a.packed) hipLaunchKernelGGL((k_gemm_deep<GLU, true, true>), dim3(grid), dim3(kDeepThreads), kDeepLds, stream, a);
-    else hipLaunchKernelGGL((k_gemm_deep<GLU, true, false>), dim3(grid), dim3(kDeepThreads), kDeepLds, stream, a);
-  } else {
-    if (a.packed) hipLaunchKernelGGL((k_gemm_deep<GLU, false, true>), dim3(grid), dim3(kDeepThreads), kDeepLds, stream, a);
-    else hipLaunchKernelGGL((k_gemm_deep<GLU, false, false>), dim3(grid), dim3(kDeepThreads), kDeepLds, stream, a);
-  }
+  if (a.packed) hipLaunchKernelGGL((k_gemm_deep<GLU, FP8, true>), dim3(grid), dim3(kDeepThreads), kDeepLds, stream, a);
+  else hipLaunchKernelGGL((k_gemm_deep<GLU, FP8, false>), dim3(grid), dim3(kDeepThreads), kDeepLds, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_deep_gemm1(const GemmArgs& a, int grid, hipStream_t stream) {
-  return launch_deep_stage<true>(a, grid, stream);
+  return launch_deep_stage<true, false>(a, grid, stream);
 }
 
 hipError_t launch_deep_gemm2(const GemmArgs& a, int grid, hipStream_t stream) {
-  return launch_deep_stage<false>(a, grid, stream);
+  return a.fp8 ? launch_deep_stage<false, true>(a, grid, stream) : launch_deep_stage<false, false>(a, grid, stream);
 }
 
 }  // namespace damoe
