@@ -21,10 +21,10 @@
 // tokens the same code runs at 1.95 GHz and 1480 TF/s instead of 1160.  Every byte moved costs there,
 // so items are ordered for L2 reuse (big_order).  Short tiles: the weight stream (5.9-6.3 TB/s).
 // Per layer call, before (8 waves, both operands in a two- or three-stage LDS ring) and now:
-//   bf16, 512 tokens per expert:  GEMM1 6.94-7.12 -> 6.65-6.91 ms, GEMM2 3.87-4.08 -> 3.52-3.65 ms
+//   bf16, 512 tokens per expert:  GEMM1 6.94-7.12 -> 6.56-6.71 ms, GEMM2 3.87-4.08 -> 3.42-3.54 ms
 //   bf16, 64 tokens per expert:   GEMM1 2.81-2.91 -> 2.41 ms
-//   Kimi-K2 shape, T = 8192, alpha = 0.3:   GEMM1 5.6 -> 5.05 ms, GEMM2 2.84 -> 2.74 ms
-//   DeepSeek-V3 fp8, T = 16384, alpha = 0.3: GEMM1 8.1 -> 7.3 ms
+//   Kimi-K2 shape, T = 8192, alpha = 0.3:   GEMM1 5.6 -> 4.95-5.05 ms, GEMM2 2.84 -> 2.65-2.70 ms
+//   DeepSeek-V3 fp8, T = 16384, alpha = 0.3: GEMM1 8.1 -> 7.2-7.4 ms
 #include <type_traits>
 
 #include "common.h"
