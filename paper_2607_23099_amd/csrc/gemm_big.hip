@@ -317,15 +317,19 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     // MFMAs.  Then a wait for this wave's token moves of stage t + 1 and its LDS reads, and the
     // barrier that makes stage t + 1 visible to every wave and frees stage t's buffer.  Moves
     // complete in issue order: after those of stage t + 1 the wave issued the moves of NT - 2
-    // stages and the loads of NT - 1 iterations (at the start of the item, those of D stages).  The barrier is a bare
-    // s_barrier: the counter waits before it are the ordering (a fence would drain the moves
-    // still ahead).  `tdst` and `tcur` are distinct buffers, so the compiler does not hold the
-    // reads behind the moves.
+    // stages and the loads of NT - 1 iterations (at the start of the item, those of D stages).
+    // The count is right only while the compiler keeps every load in it: it removes loads that
+    // nothing reads.  In the loop each feeds a later trip; the two iterations of a tail (`last`)
+    // have none, their weights being in the ring, and wait by the token moves alone, which always
+    // write LDS.  The barrier is a bare s_barrier: the counter waits before it are the ordering (a
+    // fence would drain the moves still ahead).  `tdst` and `tcur` are distinct buffers, so the
+    // compiler does not hold the reads behind the moves.
     constexpr int NW = 4 * kBigMB;  // weight loads of a stage
     constexpr int kAhead = (NT - 2) * NTOK + (NW * (NT - 1) < NW * (D + 1) - kBigMB ? NW * (NT - 1) : NW * (D + 1) - kBigMB);
-    auto iter = [&](lds_t* __restrict__ tdst, const lds_t* __restrict__ tcur, int t, auto d_c)
+    auto iter = [&](lds_t* __restrict__ tdst, const lds_t* __restrict__ tcur, int t, auto d_c, auto last_c)
         __attribute__((always_inline)) {
       constexpr int d = decltype(d_c)::value, dp = (d + D - 1) % D;
+      constexpr bool last = decltype(last_c)::value;
       uint32_t soff;
       const __amdgpu_buffer_rsrc_t rx = tok_src(t + NT - 1, soff);
       float sc_next = 0.f;
@@ -348,15 +352,17 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
           __builtin_amdgcn_sched_barrier(0);
         }
         if (s == 0) {
-          wload(dp, 3);
-          wstage(t + D);
+          if constexpr (!last) {
+            wload(dp, 3);
+            wstage(t + D);
+          }
           sc = sc_next;
         } else if (s % NH == 0) {
-          wload(d, s / NH - 1);
+          if constexpr (!last) wload(d, s / NH - 1);
         }
         __builtin_amdgcn_sched_barrier(0);
       }
-      wait_cnt<kAhead, 0>();
+      wait_cnt<last ? (NT - 2) * NTOK : kAhead, 0>();
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
     };
@@ -376,26 +382,26 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     wait_cnt<(NT - 2) * NTOK + NW * D - kBigMB, 15>();  // this wave's stage-0 moves have landed
     __syncthreads();                              // ... and every wave's, and the scales
     int t = 0;
-    auto trip = [&](auto cnt_c) __attribute__((always_inline)) {
+    auto trip = [&](auto cnt_c, auto last_c) __attribute__((always_inline)) {
       constexpr int CNT = decltype(cnt_c)::value;
-      iter(tbuf(t + NT - 1), tbuf(t), t, std::integral_constant<int, 0>{});
-      iter(tbuf(t + NT), tbuf(t + 1), t + 1, std::integral_constant<int, 1>{});
+      iter(tbuf(t + NT - 1), tbuf(t), t, std::integral_constant<int, 0>{}, last_c);
+      iter(tbuf(t + NT), tbuf(t + 1), t + 1, std::integral_constant<int, 1>{}, last_c);
       if constexpr (CNT >= 4) {
-        iter(tbuf(t + NT + 1), tbuf(t + 2), t + 2, std::integral_constant<int, 2>{});
-        iter(tbuf(t + NT + 2), tbuf(t + 3), t + 3, std::integral_constant<int, 3>{});
+        iter(tbuf(t + NT + 1), tbuf(t + 2), t + 2, std::integral_constant<int, 2>{}, last_c);
+        iter(tbuf(t + NT + 2), tbuf(t + 3), t + 3, std::integral_constant<int, 3>{}, last_c);
       }
       if constexpr (CNT == 8) {
-        iter(tbuf(t + NT + 3), tbuf(t + 4), t + 4, std::integral_constant<int, 4>{});
-        iter(tbuf(t + NT + 4), tbuf(t + 5), t + 5, std::integral_constant<int, 5>{});
-        iter(tbuf(t + NT + 5), tbuf(t + 6), t + 6, std::integral_constant<int, 6>{});
-        iter(tbuf(t + NT + 6), tbuf(t + 7), t + 7, std::integral_constant<int, 7>{});
+        iter(tbuf(t + NT + 3), tbuf(t + 4), t + 4, std::integral_constant<int, 4>{}, last_c);
+        iter(tbuf(t + NT + 4), tbuf(t + 5), t + 5, std::integral_constant<int, 5>{}, last_c);
+        iter(tbuf(t + NT + 5), tbuf(t + 6), t + 6, std::integral_constant<int, 6>{}, last_c);
+        iter(tbuf(t + NT + 6), tbuf(t + 7), t + 7, std::integral_constant<int, 7>{}, last_c);
       }
       t += CNT;
     };
     // K is a multiple of 128 (512 with fp8 weights), so the stages are a multiple of 2 (8).
-    while (t + D <= nst) trip(std::integral_constant<int, D>{});
+    while (t + D <= nst) trip(std::integral_constant<int, D>{}, std::false_type{});
     if (D == 4 && !FP8 && t < nst) {
-      trip(std::integral_constant<int, 2>{});
+      trip(std::integral_constant<int, 2>{}, std::true_type{});
       conv(NS - 1, 1);
     } else {
       conv(NS - 1, D - 1);
