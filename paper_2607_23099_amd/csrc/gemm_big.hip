@@ -51,8 +51,7 @@ constexpr uint32_t kBigRing = 128 * 1024;                      // LDS ring of to
 constexpr uint32_t kBigScaleOff = kBigRing;                    // fp8: the item's two rows of block scales
 constexpr uint32_t kBigSlotOff = kBigScaleOff + 2 * kBigMaxSk * 4;
 constexpr uint32_t kBigOrderOff = kBigSlotOff + 16;            // uint16 tile order
-constexpr int kBigMaxOrder = 8192;                             // longer lists run in list order
-constexpr size_t kBigLds = kBigOrderOff + 2 * kBigMaxOrder;
+constexpr size_t kBigLds = kBigOrderOff + 2 * kMaxSortedTiles;
 static_assert(kBigLds <= 160 * 1024, "LDS of one CU");
 
 // Per count NN of active token blocks of 32 (1 .. 8) of an item: token moves per wave and stage, token
@@ -158,8 +157,8 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
   const int2* __restrict__ ent = reinterpret_cast<const int2*>(list + 2);
   const int n_fb = (ka.N + FEAT - 1) / FEAT;
   const int l32 = lane & 31, lh = lane >> 5;
-  const ItemMap map(n_tiles, n_fb, GLU);
-  const bool sorted = GLU && n_tiles <= kBigMaxOrder && n_tiles * n_fb > (int)gridDim.x;
+  const bool sorted = GLU && sort_tiles(n_tiles, n_fb, (int)gridDim.x);
+  const ItemMap map(n_tiles, n_fb, sorted);
   if (sorted) big_order(ent, n_tiles, lds);
 
   // Items come from the per-XCD work queues.  Thread 0 takes the tickets, one item ahead, and

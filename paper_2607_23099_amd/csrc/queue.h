@@ -25,12 +25,15 @@ struct ItemMap {
   bool xcd, ends;
   int fg, tg, n_fg, nq, n_chunks;
 
-  // both_ends: odd queues run their chunks from the last to the first.  For tiles sorted by length:
-  // half the XCDs then run long tiles (bound by the matrix cores) while the others run short ones
-  // (bound by the weight stream).
-  __device__ ItemMap(int n_tiles, int n_fb, bool both_ends = false) : ends(both_ends) {
-    const int per_xcd = gridDim.x / kXcds;
-    xcd = gridDim.x % kXcds == 0 && per_xcd > 0;
+  // both_ends: odd queues run their chunks from the last to the first.  For tiles sorted by length
+  // only: half the XCDs then run long tiles (bound by the matrix cores) while the others run short
+  // ones (bound by the weight stream).  In list order it would start the odd queues with the partial
+  // last chunk and part the tiles of an expert.
+  __device__ ItemMap(int n_tiles, int n_fb, bool both_ends = false)
+      : ItemMap(n_tiles, n_fb, both_ends, (int)gridDim.x) {}
+  __host__ __device__ ItemMap(int n_tiles, int n_fb, bool both_ends, int grid) : ends(both_ends) {
+    const int per_xcd = grid / kXcds;
+    xcd = grid % kXcds == 0 && per_xcd > 0;
     fg = n_fb % 4 == 0 ? 4 : n_fb % 2 == 0 ? 2 : 1;
     if (!xcd || fg > per_xcd) fg = 1;
     tg = xcd ? per_xcd / fg : 1;
@@ -40,10 +43,10 @@ struct ItemMap {
   }
 
   // Tickets of queue q: its chunks q, q + nq, ... times tg * fg items each.
-  __device__ int queue_len(int q) const { return q < n_chunks ? ((n_chunks - 1 - q) / nq + 1) * (tg * fg) : 0; }
+  __host__ __device__ int queue_len(int q) const { return q < n_chunks ? ((n_chunks - 1 - q) / nq + 1) * (tg * fg) : 0; }
 
   // Item of ticket t of queue q; false for the slots past the last tile of a partial chunk.
-  __device__ bool item(int q, int t, int n_tiles, int& tile, int& fb) const {
+  __host__ __device__ bool item(int q, int t, int n_tiles, int& tile, int& fb) const {
     int j = t / (tg * fg);
     if (ends && (q & 1)) j = (n_chunks - 1 - q) / nq - j;
     const int chunk = q + j * nq;
@@ -54,6 +57,14 @@ struct ItemMap {
     return tile < n_tiles;
   }
 };
+
+// Whether a launch runs its tiles sorted by length (and its odd queues from the short end): where a
+// workgroup takes more than one item (before that the order changes nothing), up to the longest list
+// whose order fits the LDS beside the rings.  Longer lists run in list order from the first tile.
+constexpr int kMaxSortedTiles = 8192;
+__host__ __device__ inline bool sort_tiles(int n_tiles, int n_fb, int grid) {
+  return n_tiles <= kMaxSortedTiles && n_tiles * n_fb > grid;
+}
 
 // Thread 0's side of the queues.  take() returns queue << 28 | ticket, or -1 once every queue
 // is empty; the workgroup learns it through an LDS word (the kernels' item loops).  A

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 from paper_2607_23099_amd import damoe, synth
-from tests.gpu_common import TOL, bf16_rows, log, oracle_rows, row_err, torch_cuda
+from tests.gpu_common import TOL, bf16_rows, log, oracle_rows, row_err, tile_rows, torch_cuda
 
 pytestmark = pytest.mark.gpu
 
@@ -53,4 +53,32 @@ def test_big_tile_edges(wdtype, H, I, names, packed):
             log(f"{name} {wdtype} H={H} I={I} packed={packed}: {err:.4f}")
             # the layer's bound of its weight type: h, out and y rounded to bf16 (and h to e4m3)
             assert err <= TOL[wdtype], (name, err)
+    assert damoe.read_device_error(path.ws) == 0
+
+
+def test_more_tiles_than_a_sorted_launch_takes():
+    """A list of more than 8192 tiles of 256 rows: GEMM1 runs it in list order over many items a workgroup."""
+    torch = torch_cuda()
+    from paper_2607_23099_amd.moe import DeviceLayer, Path
+    sh = synth.Shape("many-tiles", E=18, k=16, H=128, I=256, shape_id=62)
+    T = 131400
+    rng = np.random.default_rng(9)
+    ids = rng.random((T, sh.E)).argsort(axis=1)[:, : sh.k].astype(np.int32)
+    w = rng.uniform(0.02, 0.1, (T, sh.k)).astype(np.float32)
+    r = synth.Routing(ids=ids, w=w, logp=np.zeros(sh.E), E=sh.E, k=sh.k, alpha=None)
+    path = Path(DeviceLayer(sh), T)
+    path.set_routing(r)
+    path.fill_x(T, 4)
+    path.route(T)
+    assert len(path.tiles(T, 4)) > 8192
+    rows = tile_rows(r, sh.E, n_min=128, seed=2)
+    ref = oracle_rows(sh, r, 4, rows)
+    for _ in range(2):
+        path.y.fill_(float("nan"))
+        path.fused(T, _variant("big_bm256"))
+        torch.cuda.synchronize()
+        err = row_err(bf16_rows(path.y, rows), ref)
+        log(f"{len(path.tiles(T, 4))} tiles: {err:.4f}")
+        assert err <= TOL["bf16"]
+        assert bool(torch.isfinite(path.y[:T].float()).all())
     assert damoe.read_device_error(path.ws) == 0
