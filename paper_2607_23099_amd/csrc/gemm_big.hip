@@ -232,9 +232,9 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     };
 
     // Weight operand of this wave: 32 rows, lane l row l % 32, 8 columns 8 (l / 32) .. of a
-    // 16-column k-step.  GEMM1: rows 0..15 are W1 features fb * 128 + 16 wave .., rows 16..31 the
-    // same features of W3, so gate and up of a feature meet in one lane.  GEMM2: W2 rows
-    // fb * 256 + 32 wave ..; a last item of 128 rows repeats row blocks (never stored).
+    // 16-column k-step.  GEMM1, operand m: rows 0..15 are W1 features fb * 128 + 32 wave + 16 m ..,
+    // rows 16..31 the same features of W3, so gate and up of a feature meet in one lane.  GEMM2:
+    // W2 rows fb * 256 + 64 wave + 32 m ..; a last item of 128 rows repeats row blocks (never stored).
     const size_t slab = (size_t)N * K * EB;
     gptr wp[kBigMB], wps[kBigMB];
 #pragma unroll
@@ -383,17 +383,12 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     int t = 0;
     auto trip = [&](auto cnt_c, auto last_c) __attribute__((always_inline)) {
       constexpr int CNT = decltype(cnt_c)::value;
+      static_assert(CNT == 2 || CNT == 4, "iterations of a trip");
       iter(tbuf(t + NT - 1), tbuf(t), t, std::integral_constant<int, 0>{}, last_c);
       iter(tbuf(t + NT), tbuf(t + 1), t + 1, std::integral_constant<int, 1>{}, last_c);
       if constexpr (CNT >= 4) {
         iter(tbuf(t + NT + 1), tbuf(t + 2), t + 2, std::integral_constant<int, 2>{}, last_c);
         iter(tbuf(t + NT + 2), tbuf(t + 3), t + 3, std::integral_constant<int, 3>{}, last_c);
-      }
-      if constexpr (CNT == 8) {
-        iter(tbuf(t + NT + 3), tbuf(t + 4), t + 4, std::integral_constant<int, 4>{}, last_c);
-        iter(tbuf(t + NT + 4), tbuf(t + 5), t + 5, std::integral_constant<int, 5>{}, last_c);
-        iter(tbuf(t + NT + 5), tbuf(t + 6), t + 6, std::integral_constant<int, 6>{}, last_c);
-        iter(tbuf(t + NT + 6), tbuf(t + 7), t + 7, std::integral_constant<int, 7>{}, last_c);
       }
       t += CNT;
     };
