@@ -156,6 +156,10 @@ hipError_t launch_deep_gemm2(const GemmArgs& a, int grid, hipStream_t stream);
 hipError_t launch_big_gemm1(const GemmArgs& a, int grid, hipStream_t stream);
 hipError_t launch_big_gemm2(const GemmArgs& a, int grid, hipStream_t stream);
 hipError_t big_set_lds_limits();
+// The same for row-major weights (called by the three above).
+hipError_t launch_big_rm_gemm1(const GemmArgs& a, int grid, hipStream_t stream);
+hipError_t launch_big_rm_gemm2(const GemmArgs& a, int grid, hipStream_t stream);
+hipError_t big_rm_set_lds_limits();
 // GEMM2 of the fp8-MFMA variant (its GEMM1 is the big-tile kernel's, launch_big_gemm1).
 hipError_t launch_big8_gemm2(const GemmArgs& a, int grid, hipStream_t stream);
 hipError_t big8_set_lds_limits();

@@ -1,5 +1,6 @@
 // Big-tile class of the grouped expert GEMMs (a6, a7) for prefill-sized token counts, where the
-// work is bound by the matrix cores rather than by the weight stream.
+// work is bound by the matrix cores rather than by the weight stream.  Fragment-packed weights;
+// row-major ones take gemm_big_rm.hip.
 //
 // One workgroup of 4 waves per CU, one per SIMD.  A work item is (tile of up to 256 tokens of one
 // expert, 256 weight rows): for GEMM1 the rows are 128 features of W1 (gate) and the same 128 of W3
@@ -143,7 +144,7 @@ __device__ __forceinline__ args_ptr item_args() {
 // (codes [N / 64][A][64]) and o8s (scale words [N / 64][A][4]), the operand of its fp8-MFMA
 // GEMM2, stored stage-major so that each of GEMM2's moves reads contiguous bytes.
 // rowmajor_h: bf16 h as [A][N], for the deep-ring variant's GEMM2 (fp8 weights).
-template <bool GLU, bool FP8, bool PK>
+template <bool GLU, bool FP8>
 __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx, bool rowmajor_h) {
   constexpr int FEAT = GLU ? kBigRows / 2 : kBigRows;  // output features per item
   constexpr int EB = FP8 ? 1 : 2;
@@ -241,11 +242,10 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     for (int m = 0; m < kBigMB; ++m) {
       const uint32_t rb = GLU ? (uint32_t)(fb * 8 + wave * kBigMB + m)
                               : (uint32_t)min(fb * 16 + (wave * kBigMB + m) * 2 + (l32 >> 4), N / 16 - 1);
-      const size_t woff = (size_t)e * slab + (PK ? (size_t)rb * (K / 32) * (512 * EB) + ((l32 & 15) + 16 * lh) * 8 * EB
-                                                 : ((size_t)(rb * 16 + (l32 & 15)) * K + 8 * lh) * EB);
+      const size_t woff = (size_t)e * slab + (size_t)rb * (K / 32) * (512 * EB) + ((l32 & 15) + 16 * lh) * 8 * EB;
       wp[m] = (gptr)((GLU && (l32 >> 4)) ? a->wb : a->wa) + woff;
     }
-    constexpr uint32_t kWStage = PK ? 1024 * EB : BK * EB;  // bytes from one stage to the next
+    constexpr uint32_t kWStage = 1024 * EB;  // bytes from one stage to the next
     WRaw wf[D][4][kBigMB];
     auto wstage = [&](int st) __attribute__((always_inline)) {
 #pragma unroll
@@ -253,7 +253,7 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
     };
     auto wload = [&](int d, int ks) __attribute__((always_inline)) {
       typedef uint32_t vec __attribute__((ext_vector_type(sizeof(WRaw) / 4)));
-      const uint32_t off = PK ? ((ks >> 1) * 512u + (ks & 1) * 256u) * EB : ks * 16u * EB;
+      const uint32_t off = ((ks >> 1) * 512u + (ks & 1) * 256u) * EB;
 #pragma unroll
       for (int m = 0; m < kBigMB; ++m) {
         const auto* q = reinterpret_cast<const __attribute__((address_space(1))) vec*>(wps[m] + off);
@@ -517,7 +517,7 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
   if (tid == 0) taker.finish();
 }
 
-template <bool GLU, bool FP8, bool PK>
+template <bool GLU, bool FP8>
 __global__ void __launch_bounds__(kBigThreads, 1) k_gemm_big(GemmArgs a) {
   extern __shared__ __attribute__((aligned(1024))) uint8_t big_smem[];
   flag_stale_tiles(a);
@@ -534,50 +534,36 @@ __global__ void __launch_bounds__(kBigThreads, 1) k_gemm_big(GemmArgs a) {
   const bool mx = GLU && FP8 && (v == kBig8Variant || v == kDeep8Variant);
   const bool rowmajor_h = GLU && FP8 && v == kDeepVariant;
   if (v != kBigVariant && !mx && !rowmajor_h) return;  // the device chose another kernel class
-  big_body<GLU, FP8, PK>(a, (lds_t*)big_smem, mx, rowmajor_h);
+  big_body<GLU, FP8>(a, (lds_t*)big_smem, mx, rowmajor_h);
 }
 
 template <bool GLU>
 hipError_t launch_big_stage(const GemmArgs& a, int grid, hipStream_t stream) {
-  if (a.fp8) {
-    if (a.packed) hipLaunchKernelGGL((k_gemm_big<GLU, true, true>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
-    else hipLaunchKernelGGL((k_gemm_big<GLU, true, false>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
-  } else {
-    if (a.packed) hipLaunchKernelGGL((k_gemm_big<GLU, false, true>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
-    else hipLaunchKernelGGL((k_gemm_big<GLU, false, false>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
-  }
+  if (a.fp8) hipLaunchKernelGGL((k_gemm_big<GLU, true>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
+  else hipLaunchKernelGGL((k_gemm_big<GLU, false>), dim3(grid), dim3(kBigThreads), kBigLds, stream, a);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t big_set_lds_limits() {
-  struct Fn {
-    const void* f;
-    size_t lds;
-  };
-  const Fn fns[] = {
-      {reinterpret_cast<const void*>(&k_gemm_big<true, false, false>), kBigLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, false, false>), kBigLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<true, true, false>), kBigLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, true, false>), kBigLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<true, false, true>), kBigLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, false, true>), kBigLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<true, true, true>), kBigLds},
-      {reinterpret_cast<const void*>(&k_gemm_big<false, true, true>), kBigLds}};
-  for (const Fn& f : fns) {
-    const hipError_t e = hipFuncSetAttribute(f.f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)f.lds);
+  const void* fns[] = {
+      reinterpret_cast<const void*>(&k_gemm_big<true, false>), reinterpret_cast<const void*>(&k_gemm_big<false, false>),
+      reinterpret_cast<const void*>(&k_gemm_big<true, true>), reinterpret_cast<const void*>(&k_gemm_big<false, true>)};
+  for (const void* f : fns) {
+    const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kBigLds);
     if (e != hipSuccess) return e;
   }
-  return hipSuccess;
+  return big_rm_set_lds_limits();
 }
 
+// Row-major weights take the kernel that gathers them into LDS (k_gemm_big_rm, where both are measured).
 hipError_t launch_big_gemm1(const GemmArgs& a, int grid, hipStream_t stream) {
-  return launch_big_stage<true>(a, grid, stream);
+  return a.packed ? launch_big_stage<true>(a, grid, stream) : launch_big_rm_gemm1(a, grid, stream);
 }
 
 hipError_t launch_big_gemm2(const GemmArgs& a, int grid, hipStream_t stream) {
-  return launch_big_stage<false>(a, grid, stream);
+  return a.packed ? launch_big_stage<false>(a, grid, stream) : launch_big_rm_gemm2(a, grid, stream);
 }
 
 }  // namespace damoe

@@ -31,7 +31,7 @@ def _variant(name):
 @pytest.mark.parametrize("wdtype,H,I,names", [
     ("bf16", 384, 128, ["big_bm256"]),          # 6 and 2 stages; GEMM2 rows 256 + 128
     ("bf16", 128, 1920, ["big_bm256"]),         # 2 and 30 stages; 15 feature blocks, more items than CUs
-    ("fp8", 512, 1536, ["big_bm256", "big8_bm256"]),
+    ("fp8", 512, 1536, ["big_bm256", "big8_bm256", "deep_bm64", "deep8_bm64"]),  # all with this GEMM1
 ])
 def test_big_tile_edges(wdtype, H, I, names, packed):
     torch = torch_cuda()
@@ -54,6 +54,35 @@ def test_big_tile_edges(wdtype, H, I, names, packed):
             # the layer's bound of its weight type: h, out and y rounded to bf16 (and h to e4m3)
             assert err <= TOL[wdtype], (name, err)
     assert damoe.read_device_error(path.ws) == 0
+
+
+@pytest.mark.parametrize("wdtype", ["bf16", "fp8"])
+def test_row_major_weights_keep_up(wdtype):
+    """A few tokens on each of 48 experts: the layer call on row-major weights against packed ones.  Gathered
+    into LDS they take 1.4-1.7 times as long; loaded straight into MFMA operands it was 2.6-3.4 times."""
+    torch = torch_cuda()
+    from paper_2607_23099_amd.moe import DeviceLayer, Path
+    sh = synth.Shape(f"rows-{wdtype}", E=48, k=8, H=7168, I=2048, shape_id=63, wdtype=wdtype)
+    T = 64
+    r = synth.routing(sh.E, sh.k, T, 10.0, [64])
+    times = []
+    for packed in (True, False):
+        path = Path(DeviceLayer(sh, packed=packed), T)
+        path.set_routing(r)
+        path.fill_x(T, 5)
+        path.route(T)
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(10)]
+        path.fused(T, _variant("big_bm256"))
+        for a, b in zip(ev[::2], ev[1::2]):
+            a.record()
+            path.fused(T, _variant("big_bm256"))
+            b.record()
+        torch.cuda.synchronize()
+        times.append(np.median([a.elapsed_time(b) for a, b in zip(ev[::2], ev[1::2])]))
+        assert damoe.read_device_error(path.ws) == 0
+        del path
+    log(f"{wdtype} T={T}: packed {times[0]:.3f} ms, row-major {times[1]:.3f} ms")
+    assert times[1] <= 2.1 * times[0]
 
 
 def test_more_tiles_than_a_sorted_launch_takes():
