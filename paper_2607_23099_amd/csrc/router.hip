@@ -419,48 +419,79 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
 }
 
 // Top-k selection and gates of token t from the E logits the wave holds (expert lane + 64 j
-// in v[j], bit j of `left` set where that expert exists).  Each lane first sorts its experts, by
-// falling key and rising id, so a round looks at one value a lane: the wave's largest key wins, among
-// equal keys the lowest expert id, and the winner's lane moves its list up.  (Scanning every lane's
-// values each round took 700 VALU instructions a token, and at T = 8192 bounded the kernel.)  The
-// rounds are a loop, not unrolled: the kernel stays small, so a block's first instruction fetches
+// in v[j], bit j of `left` set where that expert exists).  Each round takes the largest key left, among
+// equal keys the lowest expert id.
+//   SORT: each lane first sorts its experts, by falling key and rising id, so a round looks at one value a
+//   lane, and the winner's lane moves its list up.
+//   Else a round scans every lane's values, and ballots find the winner (smallest j, then lowest lane).
+// The sort costs NJ^2 / 2 exchanges of 64-bit keys, a round of the scan about 3 NJ operations, so the
+// sort pays from k = NJ / 2 rounds on.  One token, call with scan / sort: E = 512, k = 2 8.3 / 10.2 us,
+// k = 4 9.2 / 8.8, k = 16 13.7 / 11.2; E = 1024, k = 8 14.7 / 14.1; E = 64 (one value a lane) 8.5 / 8.7.
+// The rounds are a loop, not unrolled: the kernel stays small, so a block's first instruction fetches
 // are few.
-template <int NJ>
+template <int NJ, bool SORT>
 __device__ __forceinline__ void select_topk(const float (&v)[NJ], uint32_t left, int lane, int t,
                                             const TopkArgs& a) {
-  // Key in the high word, the id's complement in the low word; 0 where there is no expert (a NaN's
-  // key may be 0, its low word is not).
-  uint64_t c[NJ];
-#pragma unroll
-  for (int j = 0; j < NJ; ++j)
-    c[j] = ((left >> j) & 1u) ? (uint64_t)float_key(v[j]) << 32 | (uint32_t)~(kWave * j + lane) : 0ull;
-  // Odd-even transposition sort, falling.
-#pragma unroll
-  for (int p = 0; p < NJ; ++p)
-#pragma unroll
-    for (int j = p & 1; j + 1 < NJ; j += 2) {
-      const bool sw = c[j + 1] > c[j];
-      const uint64_t x = sw ? c[j + 1] : c[j], y = sw ? c[j] : c[j + 1];
-      c[j] = x;
-      c[j + 1] = y;
-    }
   int32_t my_id = 0;
   uint32_t my_key = 0;
-#pragma unroll 1
-  for (int r = 0; r < a.k; ++r) {
-    const uint32_t key = (uint32_t)(c[0] >> 32), low = (uint32_t)c[0];
-    const uint32_t m = wave_max_u32(key);
-    const uint64_t hold = __ballot(key == m);
-    uint32_t win = (uint32_t)__builtin_amdgcn_readlane((int)low, (int)__builtin_ctzll(hold));
-    if (m == 0 || (hold & (hold - 1)) != 0) win = wave_max_u32(key == m ? low : 0u);  // ties
-    if (lane == r) {
-      my_id = (int32_t)~win;
-      my_key = m;
-    }
-    if (low == win && key == m) {
+  if constexpr (SORT) {
+    // Key in the high word, the id's complement in the low word; 0 where there is no expert (a NaN's
+    // key may be 0, its low word is not).
+    uint64_t c[NJ];
 #pragma unroll
-      for (int j = 0; j + 1 < NJ; ++j) c[j] = c[j + 1];
-      c[NJ - 1] = 0ull;
+    for (int j = 0; j < NJ; ++j)
+      c[j] = ((left >> j) & 1u) ? (uint64_t)float_key(v[j]) << 32 | (uint32_t)~(kWave * j + lane) : 0ull;
+    // Odd-even transposition sort, falling.
+#pragma unroll
+    for (int p = 0; p < NJ; ++p)
+#pragma unroll
+      for (int j = p & 1; j + 1 < NJ; j += 2) {
+        const bool sw = c[j + 1] > c[j];
+        const uint64_t x = sw ? c[j + 1] : c[j], y = sw ? c[j] : c[j + 1];
+        c[j] = x;
+        c[j + 1] = y;
+      }
+#pragma unroll 1
+    for (int r = 0; r < a.k; ++r) {
+      const uint32_t key = (uint32_t)(c[0] >> 32), low = (uint32_t)c[0];
+      const uint32_t m = wave_max_u32(key);
+      const uint64_t hold = __ballot(key == m);
+      uint32_t win = (uint32_t)__builtin_amdgcn_readlane((int)low, (int)__builtin_ctzll(hold));
+      if (m == 0 || (hold & (hold - 1)) != 0) win = wave_max_u32(key == m ? low : 0u);  // ties
+      if (lane == r) {
+        my_id = (int32_t)~win;
+        my_key = m;
+      }
+      if (low == win && key == m) {
+#pragma unroll
+        for (int j = 0; j + 1 < NJ; ++j) c[j] = c[j + 1];
+        c[NJ - 1] = 0ull;
+      }
+    }
+  } else {
+    uint32_t key[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) key[j] = float_key(v[j]);
+#pragma unroll 1
+    for (int r = 0; r < a.k; ++r) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j)
+        if ((left >> j) & 1u) m = max(m, key[j]);
+      m = wave_max_u32(m);
+      int32_t e = -1;
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        if (e < 0) {
+          const uint64_t hold = __ballot(((left >> j) & 1u) && key[j] == m);
+          if (hold) e = kWave * j + (int32_t)__builtin_ctzll(hold);
+        }
+      }
+      if ((e & (kWave - 1)) == lane) left &= ~(1u << (e / kWave));
+      if (lane == r) {
+        my_id = e;
+        my_key = m;
+      }
     }
   }
   const float top = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, key_float(my_key)), 0));
@@ -476,7 +507,7 @@ __device__ __forceinline__ void select_topk(const float (&v)[NJ], uint32_t left,
 
 // Few splits (many tokens): one wave per token sums its experts' S partials in split order.
 // NJ = 64-expert groups held per lane (ceil(E / 64) rounded up to a power of two).
-template <int NJ>
+template <int NJ, bool SORT>
 __global__ __launch_bounds__(256) void k_router_topk_wave(TopkArgs a) {
   pin(a.part);
   pin(a.bias);
@@ -499,17 +530,19 @@ __global__ __launch_bounds__(256) void k_router_topk_wave(TopkArgs a) {
   }
   const float* p = a.part + (size_t)t * a.E + lane;
   const size_t split = (size_t)a.T * a.E;
-  // Four splits' loads in flight at a time, added in split order.
+  // Four splits' loads in flight at a time, added in split order (above 512 experts there is one split,
+  // rarely two).
+  constexpr int B = NJ <= 8 ? 4 : 1;
 #pragma unroll 1
-  for (int s0 = 0; s0 < a.S; s0 += 4) {
-    float q[4][NJ];
+  for (int s0 = 0; s0 < a.S; s0 += B) {
+    float q[B][NJ];
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < B; ++u)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         q[u][j] = (s0 + u < a.S && ((left >> j) & 1u)) ? p[(size_t)(s0 + u) * split + kWave * j] : 0.0f;
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < B; ++u)
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
         if (s0 + u < a.S) v[j] += q[u][j];
@@ -522,16 +555,17 @@ __global__ __launch_bounds__(256) void k_router_topk_wave(TopkArgs a) {
       if (a.logits) a.logits[(size_t)t * a.E + e] = v[j];
     }
   }
-  select_topk<NJ>(v, left, lane, t, a);
+  select_topk<NJ, SORT>(v, left, lane, t, a);
 }
 
 // Many splits (few tokens): a block per token.  Each thread sums MB = NJ / 4 experts over the
-// S partials in split order, B splits' loads in flight at a time (the whole sum in one
-// round trip for S <= 32 at E <= 512); the logits meet in LDS and the first wave selects.
-template <int NJ>
+// S partials in split order, 32 / MB splits' loads in flight at a time (with 64 / MB the whole sum of 28
+// splits is one round trip, yet E = 384 and 512 ran 0.6-0.8 us slower); the logits meet in LDS and the
+// first wave selects.
+template <int NJ, bool SORT>
 __global__ __launch_bounds__(256) void k_router_topk_block(TopkArgs a) {
   constexpr int MB = NJ >= 4 ? NJ / 4 : 1;
-  constexpr int B = MB == 1 ? 32 : 64 / MB;
+  constexpr int B = 32 / MB;
   __shared__ float lg[NJ * kWave];
   pin(a.part);
   pin(a.bias);
@@ -584,16 +618,24 @@ __global__ __launch_bounds__(256) void k_router_topk_block(TopkArgs a) {
       left |= 1u << j;
     }
   }
-  select_topk<NJ>(w, left, lane, t, a);
+  select_topk<NJ, SORT>(w, left, lane, t, a);
+}
+
+template <int NJ, bool SORT>
+hipError_t launch_topk_as(const TopkArgs& ta, bool per_block, hipStream_t stream) {
+  if (per_block)
+    hipLaunchKernelGGL((k_router_topk_block<NJ, SORT>), dim3(ta.T), dim3(256), 0, stream, ta);
+  else
+    hipLaunchKernelGGL((k_router_topk_wave<NJ, SORT>), dim3((ta.T + 3) / 4), dim3(256), 0, stream, ta);
+  return hipGetLastError();
 }
 
 template <int NJ>
 hipError_t launch_topk(const TopkArgs& ta, bool per_block, hipStream_t stream) {
-  if (per_block)
-    hipLaunchKernelGGL(k_router_topk_block<NJ>, dim3(ta.T), dim3(256), 0, stream, ta);
-  else
-    hipLaunchKernelGGL(k_router_topk_wave<NJ>, dim3((ta.T + 3) / 4), dim3(256), 0, stream, ta);
-  return hipGetLastError();
+  if constexpr (NJ > 1) {
+    if (2 * ta.k >= NJ) return launch_topk_as<NJ, true>(ta, per_block, stream);
+  }
+  return launch_topk_as<NJ, false>(ta, per_block, stream);
 }
 
 struct Plan {

@@ -174,6 +174,67 @@ def test_router_ties_and_zero_tokens():
     _check_selection(lg, ids, w, k)
 
 
+@pytest.mark.parametrize("H", [64, 1024], ids=["wave", "block"])  # one split: a wave a token; four: a block
+@pytest.mark.parametrize("E,k", [(64, 1), (64, 16), (65, 1), (128, 2), (129, 1), (256, 1), (129, 2), (256, 2),
+                                 (257, 3), (512, 3), (257, 4), (512, 4), (513, 7), (1024, 7), (513, 8), (1024, 16)])
+def test_selection_by_scan_and_by_sorted_lists(E, k, H):
+    # Zero tokens make the logits the bias, so the selection is exact: ties, both zeros, the type's lowest
+    # value and infinities, at both sides of k = ceil(E / 64) / 2 (rounded up to a power of two).
+    torch = torch_cuda()
+    rng = np.random.default_rng(1000 * E + k)
+    T = 3
+    x = torch.zeros((T, H), dtype=torch.bfloat16, device="cuda")
+    wg = _dev_bf16(synth.f32_to_bf16_bits(rng.normal(0, 1, (E, H))))
+    ties = rng.integers(-3, 3, E).astype(np.float32)
+    edge = np.where(rng.random(E) < 0.5, np.float32(-0.0), np.float32(0.0))
+    edge[rng.integers(0, E, E // 2)] = np.finfo(np.float32).min
+    inf = rng.normal(0, 1, E).astype(np.float32)
+    inf[rng.permutation(E)[: E // 8]] = -np.inf
+    inf[rng.permutation(E)[0]] = np.inf
+    for name, bias in (("normal", rng.normal(0, 1, E).astype(np.float32)), ("ties", ties), ("edge", edge), ("inf", inf),
+                       ("last", np.arange(E, dtype=np.float32))):
+        lg, ids, w = _router(x, wg, torch.from_numpy(bias).cuda(), T, H, E, k)
+        np.testing.assert_array_equal(lg, np.tile(bias, (T, 1)) + np.float32(0), err_msg=name)
+        want = np.argsort(-(bias + np.float32(0)), kind="stable")[:k]  # the lower id first among equals
+        np.testing.assert_array_equal(ids, np.tile(want, (T, 1)), err_msg=name)
+        if name != "inf":
+            top = bias[want].astype(np.float64)
+            ex = np.exp(top - top[0])
+            np.testing.assert_allclose(w, np.tile(ex / ex.sum(), (T, 1)), rtol=4 * k * U * 8, atol=1e-7, err_msg=name)
+
+
+def test_few_choices_cost_less_than_many():
+    # One of 512 experts against 16 of them: 7.9 and 11.2 us. With lists sorted whatever k, 10.1 and 11.2.
+    torch = torch_cuda()
+    H, E, T = 2048, 512, 1
+    x, wg, bias = _host_case(T, H, E, 47, 0.5)
+    xd, wd, bd = _dev_bf16(x), _dev_bf16(wg), torch.from_numpy(bias).cuda()
+    ws = torch.empty(damoe.router_workspace_size(E, H, T), dtype=torch.uint8, device="cuda")
+    us = {}
+    for k in (1, 16):
+        ids = torch.empty((T, k), dtype=torch.int32, device="cuda")
+        w = torch.empty((T, k), dtype=torch.float32, device="cuda")
+        s = torch.cuda.Stream()
+        s.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(s):
+            damoe.router(xd, wd, bd, T, H, E, k, None, ids, w, ws)
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=s):
+                for _ in range(50):
+                    damoe.router(xd, wd, bd, T, H, E, k, None, ids, w, ws)
+        torch.cuda.synchronize()
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(22)]
+        for a, b in zip(ev[::2], ev[1::2]):
+            a.record()
+            g.replay()
+            b.record()
+        torch.cuda.synchronize()
+        us[k] = min(a.elapsed_time(b) for a, b in zip(ev[2::2], ev[3::2])) * 1e3 / 50
+    log(f"router E={E}: {us}")
+    assert us[1] <= 0.8 * us[16]
+
+
 def test_router_deterministic_and_empty():
     torch = torch_cuda()
     T, H, E, k = 96, 7168, 256, 8
