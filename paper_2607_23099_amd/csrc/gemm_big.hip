@@ -159,7 +159,7 @@ __device__ __forceinline__ void big_body(const GemmArgs& ka, lds_t* lds, bool mx
   const int n_fb = (ka.N + FEAT - 1) / FEAT;
   const int l32 = lane & 31, lh = lane >> 5;
   const bool sorted = GLU && sort_tiles(n_tiles, n_fb, (int)gridDim.x);
-  const ItemMap map(n_tiles, n_fb, sorted);
+  const ItemMap map(n_tiles, n_fb, GLU && both_ends(n_tiles, n_fb, (int)gridDim.x, FP8));
   if (sorted) big_order(ent, n_tiles, lds);
 
   // Items come from the per-XCD work queues.  Thread 0 takes the tickets, one item ahead, and
