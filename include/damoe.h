@@ -300,10 +300,10 @@ uint32_t damoe_table_effexp_candidates(const damoe_table* table, int32_t T);
  * must stay below 2^31 (32-bit row offsets), else DAMOE_ERR_UNSUPPORTED; so must
  * H and I of fp8 layers stay <= 16384 when a big-tile or deep-ring variant may run, and
  * T k I below 2^31 when an fp8-MFMA variant may.
- * The fp8-MFMA variants (fp8 weights only: big8_bm256 and deep8_bm64; with fp8 weights GEMM1 of
- * both, and of deep_bm64, is the big-tile kernel's) compute GEMM1 as the big-tile variant, then store h
- * (rounded to bf16) as OCP e4m3 with one E8M0 scale per 32
- * features of a row (the smallest power of two that maps the block's largest magnitude
+ * The fp8-MFMA variants (fp8 weights only: big8_bm256 and deep8_bm64, the same kernels; with fp8
+ * weights their GEMM1, and deep_bm64's, is the big-tile kernel's) compute GEMM1 as the big-tile
+ * variant, then store h (rounded to bf16) as OCP e4m3 with one E8M0 scale per 32 features of a
+ * row (the smallest power of two that maps the block's largest magnitude
  * to at most 448; round to nearest even), and GEMM2 as fp8 x fp8 MFMA on those codes and
  * the fp8 W2 with its 128x128 block scales (Sec. II-C's low-precision kernels): y carries
  * that quantisation of h besides fp32 accumulation, within the fp8 tolerance of y. */
@@ -358,14 +358,15 @@ damoe_status damoe_pack_weights(const damoe_layer* src /* host */, void* w1, voi
                                 hipStream_t stream);
 
 /* Variant registry.  Variant v computes with token tiles of
- * damoe_variant_tile_m(v) rows.  Variants are only ever appended, so an id keeps its
+ * damoe_variant_tile_m(v) rows (deep_bm64 on fp8 weights: GEMM2 only, its GEMM1 takes 256).
+ * deep8_bm64 is a second name of big8_bm256's kernels.  Variants are only ever appended, so an id keeps its
  * meaning across library versions (damoe_table_load accepts a table written by a
  * library whose variants are a prefix of this one's). */
 int32_t damoe_num_variants(void);
 const char* damoe_variant_name(int32_t v);
 int32_t damoe_variant_tile_m(int32_t v);
-/* 1 if variant v supports the layer's weight dtype: every variant runs fp8 weights, all
- * but big8_bm256 run bf16, the stream variants with tiles of at most 32 rows run MXFP4. */
+/* 1 if variant v supports the layer's weight dtype: every variant runs fp8 weights, all but
+ * big8_bm256 and deep8_bm64 run bf16, the stream variants with tiles of at most 32 rows run MXFP4. */
 int32_t damoe_variant_supports(int32_t v, int32_t wdtype);
 
 /* Offline auto-tuning (Sec. IV-A, Fig. of the dispatch flow steps 1-4). */

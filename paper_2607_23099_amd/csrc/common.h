@@ -51,7 +51,7 @@ enum VariantKind : int32_t {
   kBig = 2,     // own kernel, one workgroup per CU: tokens in LDS, weights in registers, 256 x 256 items
   kBig8 = 3,    // fp8 weights: big-tile GEMM1 writing MX-fp8 h, own fp8 x fp8 MFMA GEMM2 kernel
   kDeep = 4,    // own kernel, one workgroup per CU: tokens in LDS, weights per wave in a deep ring
-  kDeep8 = 5,   // fp8 weights: runs the kernels of kBig8
+  kDeep8 = 5,   // fp8 weights: a second name of kBig8 (same kernels, same 256-token tiles)
 };
 
 // Id of the big-tile variant (its kernel is launched separately from the others).
@@ -62,8 +62,8 @@ constexpr int32_t kBig8Variant = 8;
 
 // Id of the deep-ring variant (its kernel is launched separately from the others).
 constexpr int32_t kDeepVariant = 9;
-// Id of the fp8-MFMA deep-ring variant (fp8 weights only): GEMM1 on the big-tile kernel, as
-// kDeepVariant's with fp8 weights, GEMM2 on the fp8-MFMA kernel of kBig8Variant.
+// Id that tables of earlier libraries hold for the fp8-MFMA variant with a deep-ring GEMM1 (fp8 weights
+// only): runs what kBig8Variant runs.  The tuner neither times nor picks it.
 constexpr int32_t kDeep8Variant = 10;
 
 // Largest token tile of the MXFP4 stream kernel.

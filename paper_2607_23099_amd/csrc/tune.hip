@@ -218,16 +218,15 @@ void exemplar(const std::vector<std::vector<int32_t>>& counts, int32_t E, int32_
 
 // The kernel class a variant runs on, of the kClasses that a fused call launches separately:
 // the stream and tiled variants share one kernel, the big-tile, fp8-MFMA and deep-ring
-// variants have kernels of their own, and the fp8-MFMA deep-ring variant, which runs the
-// deep-ring GEMM1 and the fp8-MFMA GEMM2, counts as a class of its own.  A fused call whose candidates span several classes
-// launches all of them, and those the device did not choose return at once.
-constexpr int32_t kClasses = 5;
+// variants have kernels of their own (two ids name the fp8-MFMA one).  A fused call whose candidates
+// span several classes launches all of them, and those the device did not choose return at once.
+constexpr int32_t kClasses = 4;
 int32_t kernel_class(int32_t v) {
   switch (damoe::variant(v).kind) {
     case damoe::kBig: return 1;
-    case damoe::kBig8: return 2;
+    case damoe::kBig8:
+    case damoe::kDeep8: return 2;
     case damoe::kDeep: return 3;
-    case damoe::kDeep8: return 4;
     default: return 0;
   }
 }
@@ -391,6 +390,10 @@ damoe_status damoe_tune(const damoe_layer* L, const damoe_tune_config* cfg, damo
       std::vector<float> reps(cfg->reps);
       for (int32_t v = 0; v < nv; ++v) {
         if (!damoe_variant_supports(v, L->wdtype)) continue;
+        if (v == damoe::kDeep8Variant) {  // the same kernels as kBig8Variant: equal times, the lower id wins
+          lat_v[v] = lat_v[damoe::kBig8Variant];
+          continue;
+        }
         // warm-up
         s2 = damoe_fused_moe(L, cfg->x, d_w, T, d_perm, d_inv, nullptr, v, 0u, d_y, ws, ws_bytes, stream);
         if (s2 != DAMOE_OK) return s2;

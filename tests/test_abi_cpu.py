@@ -52,6 +52,8 @@ def test_status_strings_and_registry():
     assert [v for v in range(nv) if not damoe.variant_supports(v, damoe.W_BF16)] == fp8_only
     assert not any(damoe.variant_supports(v, damoe.W_MXFP4) for v in fp8_only)
     assert not damoe.variant_supports(0, 7)
+    # deep8_bm64 names the kernels of big8_bm256, tiles included.
+    assert damoe.variant_tile_m(fp8_only[0]) == damoe.variant_tile_m(fp8_only[1]) == 256
 
 
 def test_table_signature_prefix(tmp_path):

@@ -1,7 +1,7 @@
-"""GPU check of the fp8-MFMA variants' h quantisation: their GEMM1 (the big-tile kernel for
-big8_bm256, the deep-ring kernel for deep8_bm64) writes h rounded to bf16, then as e4m3 codes with
-one E8M0 scale per 32 features of a row (stage-major, in 4-byte words per 64 features).  The same
-kernel with the bf16-h variant (big_bm256: h stage-major; deep_bm64: h row-major) stores the bf16 h
+"""GPU check of the fp8-MFMA variants' h quantisation: their GEMM1 (the big-tile kernel for both
+big8_bm256 and deep8_bm64, which name the same kernels) writes h rounded to bf16, then as e4m3 codes
+with one E8M0 scale per 32 features of a row (stage-major, in 4-byte words per 64 features).  The same
+kernel with a bf16-h variant (big_bm256: h stage-major; deep_bm64: h row-major) stores the bf16 h
 itself, from the same accumulation, so the codes and scales must equal those of the test-side MX
 quantiser (tests/mx_ref.py, written from the OCP formats) applied to that bf16 h, bit for bit."""
 import numpy as np
@@ -59,6 +59,13 @@ def test_h_quantised_bit_exact(small_fp8, pair, T, alpha, seed):
     q = q.transpose(1, 0, 2).reshape(A, sh.I)
     s = path.ws[lo["h"] + A * sh.I: lo["h"] + A * sh.I + A * sh.I // 16].cpu().numpy().reshape(sh.I // 64, A, 4)
     s = s[:, :, :2].transpose(1, 0, 2).reshape(A, sh.I // 32)
+    # The other name of these kernels leaves the same bytes: codes, and bytes 0 and 1 of the scale words.
+    hw = path.ws[lo["h"]: lo["h"] + A * sh.I + A * sh.I // 16].clone()
+    path.fused_stage(0, T, names.index("big8_bm256" if pair[1] == "deep8_bm64" else "deep8_bm64"))
+    torch.cuda.synchronize()
+    other = path.ws[lo["h"]: lo["h"] + A * sh.I + A * sh.I // 16]
+    assert torch.equal(other[: A * sh.I], hw[: A * sh.I])
+    assert torch.equal(other[A * sh.I:].view(-1, 4)[:, :2], hw[A * sh.I:].view(-1, 4)[:, :2])
     assert np.all(np.isfinite(h))
     q_ref, s_ref = mx_quantise(h)
     np.testing.assert_array_equal(s, s_ref)

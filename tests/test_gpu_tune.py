@@ -95,3 +95,17 @@ def test_tune_expert_parallel_rank():
         damoe.tune(dl.layer, [1], [1.1], x, samples=1, reps=1, ep=4, repeat_f=[50])
     del dl
     torch.cuda.empty_cache()
+
+
+def test_tune_fp8_picks_one_id_of_a_kernel():
+    # Two ids name the fp8-MFMA kernels; the tuner takes the lower one and never splits a bucket over both.
+    torch = torch_cuda()
+    from paper_2607_23099_amd.moe import DeviceLayer
+    sh = synth.Shape("small-fp8-tune", E=4, k=2, H=512, I=512, shape_id=8, wdtype="fp8")
+    dl = DeviceLayer(sh)
+    x = torch.empty((600, sh.H), dtype=torch.bfloat16, device="cuda")
+    synth.fill_bf16_device(x.data_ptr(), x.numel(), seed=synth.x_seed(3), tensor=synth.T_X, slab_elems=x.numel(),
+                           sigma=1.0, stream=torch.cuda.current_stream().cuda_stream)
+    td = damoe.tune(dl.layer, [1, 64, 600], [1.1, 2.0, 4.0], x, samples=2, reps=1, seed=9).data(sh.E)
+    other = [damoe.variant_name(v) for v in range(damoe.num_variants())].index("deep8_bm64")
+    assert other not in td.kid and other not in td.noda
