@@ -529,8 +529,8 @@ __global__ void __launch_bounds__(kBigThreads, 1) k_gemm_big(GemmArgs a) {
   }
   // This kernel runs the big-tile variant and, with fp8 weights, GEMM1 of both fp8-MFMA variants and
   // of the deep-ring variant.  The deep-ring kernel's own fp8 GEMM1 decoded each weight operand for
-  // tiles of 64 tokens and padded them to 16: DeepSeek-V3 shape, T = 1024, alpha = 1, 1626 us against
-  // 1440 us here; at 64 tokens an expert, its best case, 1557 against 1577 us.
+  // tiles of 64 tokens and padded them to 16: DeepSeek-V3 shape, T = 1024, alpha = 1, 1656 us against
+  // 1408 us here; at 64 tokens an expert, its best case, 1483 against 1468 us.
   const bool mx = GLU && FP8 && (v == kBig8Variant || v == kDeep8Variant);
   const bool rowmajor_h = GLU && FP8 && v == kDeepVariant;
   if (v != kBigVariant && !mx && !rowmajor_h) return;  // the device chose another kernel class

@@ -2,18 +2,18 @@
 // per token and the softmax over them.  Its cost belongs to the end-to-end layer the paper
 // times inside one graph (Sec. V-C).
 //
-// Two kernels, both deterministic:
-//   k_router_logits  bf16 MFMA 32x32x16 over (token tile, 64-expert tile, K split); the waves
-//                    of a block either split the block's K range four ways (few tokens: the
-//                    gate matrix is the traffic, so it is spread over many blocks) or own
-//                    32-token slices of a 128-token tile, two waves per slice along K (many
-//                    tokens: the gate tile is shared through L1, a 3-deep register ring keeps
-//                    two steps of loads in flight per wave).
-//                    Partial sums go to the workspace as fp32 [S][T][E].
-//   k_router_topk_*  sums the S partials in split order (a block per token when S is large,
-//                    a wave per token otherwise), adds the bias, selects the top k with an
-//                    order-preserving integer key (ties to the lower expert id) and writes ids
-//                    and softmax gates.
+// Two kernels a call, both deterministic.  The logits (bf16 MFMA 32x32x16, fp32 partial sums [S][T][E] in
+// the workspace) come from one of three:
+//   k_router_logits<1, 4, 2>  few tokens: 32 tokens x 64 experts a block, whose 4 waves split the
+//                             block's K range; the gate matrix is the traffic, so it is spread over
+//                             many blocks.
+//   k_router_logits_lds       from 8 tiles of 128 tokens on, up to 512 experts: 128 tokens x all
+//                             experts a block, both operands through LDS rings.
+//   k_router_logits<4, 2, 3>  many tokens and more experts: 128 tokens x 64 experts a block, two waves
+//                             per 32-token slice along K, the gate tile shared through L1.
+// Then k_router_topk_* sums the S partials in split order (a block per token when S is large, a wave per
+// token otherwise), adds the bias, selects the top k with an order-preserving integer key (ties to the
+// lower expert id) and writes ids and softmax gates.
 #include <type_traits>
 
 #include "common.h"
