@@ -1,4 +1,6 @@
 """The counted waits of the big-tile kernels against the operations in the built code (CPU)."""
+import os
+
 import pytest
 
 from paper_2607_23099_amd import build
@@ -9,6 +11,8 @@ KERNEL = "k_gemm_big"
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
+    if not os.path.exists(build.LIB_DAMOE):
+        build.build_damoe()
     code = disassemble(build.LIB_DAMOE, str(tmp_path_factory.mktemp("code")), KERNEL + "I")
     assert len(code) == 4  # GEMM1 / GEMM2, bf16 / fp8
     return code
