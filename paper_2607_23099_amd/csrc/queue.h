@@ -58,9 +58,9 @@ struct ItemMap {
   }
 };
 
-// Whether a launch runs its tiles sorted by length: where a
-// workgroup takes more than one item (before that the order changes nothing), up to the longest list
-// whose order fits the LDS beside the rings.  Longer lists run in list order from the first tile.
+// Whether a launch runs its tiles sorted by length: where a workgroup takes more than one item (before
+// that the order changes nothing), up to the longest list whose order fits the LDS beside the rings.
+// Longer lists run in list order from the first tile.
 constexpr int kMaxSortedTiles = 8192;
 __host__ __device__ inline bool sort_tiles(int n_tiles, int n_fb, int grid) {
   return n_tiles <= kMaxSortedTiles && n_tiles * n_fb > grid;
@@ -68,9 +68,9 @@ __host__ __device__ inline bool sort_tiles(int n_tiles, int n_fb, int grid) {
 // Whether such a launch runs its odd queues from the short end: bf16 weights, from 7 items a workgroup on.
 // Before that the long tiles that the odd queues start last stick out at the end, and fp8 weights, half
 // the bytes, leave little to gain from short tiles beside long ones.  GEMM1 from both ends against from
-// the long end only, DeepSeek-V3 shape: fp8, 3 to 4 items a workgroup (T = 150-350, alpha = 0.04-0.06) 342-443
-// against 295-398 us, above 9 items within 2% with the long end ahead on average; bf16, 7 to 14 items
-// with tiles of mixed length 1-6% faster from both ends, 3 to 6.5 items 1-5% slower.
+// the long end only, DeepSeek-V3 shape, tiles of mixed length: fp8, 3 to 4 items a workgroup
+// (T = 150-350, alpha = 0.04-0.06) 335-443 against 294-398 us, from 9 items on within 4% either way; bf16,
+// 7 to 14 items 1-6% faster from both ends, below 7 items between 5% slower and 2% faster.
 __host__ __device__ inline bool both_ends(int n_tiles, int n_fb, int grid, bool fp8) {
   return !fp8 && sort_tiles(n_tiles, n_fb, grid) && n_tiles * n_fb >= 7 * grid;
 }
